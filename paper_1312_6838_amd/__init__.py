@@ -330,13 +330,13 @@ def quantize_tensor(A32, m, dtype, stream=None):
     n, lda = A32.shape
     if dtype == "bf16":
         ldo = ((m + 127) // 128) * 128
-        out = torch.zeros(n, ldo, dtype=torch.int16, device=A32.device)
+        out = torch.empty(n, ldo, dtype=torch.int16, device=A32.device)  # pads are written too
         quantize(A32.data_ptr(), m, n, lda, BF16, out.data_ptr(), ldo, None, _stream_ptr(stream))
         return out, None
     if dtype == "fp8":
         ldo = ((m + 255) // 256) * 256
-        out = torch.zeros(n, ldo, dtype=torch.uint8, device=A32.device)
-        sc = torch.zeros(n, dtype=torch.float32, device=A32.device)
+        out = torch.empty(n, ldo, dtype=torch.uint8, device=A32.device)
+        sc = torch.empty(n, dtype=torch.float32, device=A32.device)
         quantize(A32.data_ptr(), m, n, lda, FP8_E4M3, out.data_ptr(), ldo, sc.data_ptr(),
                  _stream_ptr(stream))
         return out, sc
