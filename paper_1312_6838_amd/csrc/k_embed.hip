@@ -132,7 +132,12 @@ __global__ __launch_bounds__(256) void k_wgram_part(const float *__restrict__ w,
 }
 
 // G (L x L, both triangles) = sum of the splits in order; padding rows and
-// columns 0 with -1 on the diagonal; U = I.
+// columns 0 with -1 on the diagonal; U = I.  One thread per entry of a tile,
+// kRedU of its partials in flight: the kernel is bound by their latency (with
+// one workgroup per tile and the loads one after another, 341 splits of 3
+// tiles took 1187 us, now 16 us).  In a diagonal tile the entries on and below
+// the diagonal decide (the two halves of a product W V^T may round apart).
+constexpr int kRedU = 32;
 __global__ __launch_bounds__(256) void k_wgram_reduce(const double *__restrict__ part, int nsplit,
                                                       int nt, int l, double *__restrict__ G,
                                                       double *__restrict__ U) {
@@ -145,17 +150,26 @@ __global__ __launch_bounds__(256) void k_wgram_reduce(const double *__restrict__
   }
   const int b = a + rem;
   const int L = nt * 64;
-  for (int e = threadIdx.x; e < 4096; e += 256) {
-    const int i = e >> 6, j = e & 63;
-    const int x = a * 64 + i, y = b * 64 + j;
-    double s = 0.0;
-    for (int sp = 0; sp < nsplit; ++sp) s += part[((int64_t)sp * ntiles + tile) * 4096 + e];
-    if (x >= l || y >= l) s = (x == y) ? -1.0 : 0.0;
-    G[(int64_t)x * L + y] = s;
-    G[(int64_t)y * L + x] = s;
-    U[(int64_t)x * L + y] = x == y ? 1.0 : 0.0;
-    U[(int64_t)y * L + x] = x == y ? 1.0 : 0.0;
+  const int e = blockIdx.y * 256 + threadIdx.x;
+  const int i = e >> 6, j = e & 63;
+  if (a == b && i < j) return;
+  const int x = a * 64 + i, y = b * 64 + j;
+  const double *src = part + (int64_t)tile * 4096 + e;
+  const int64_t step = (int64_t)ntiles * 4096;
+  double s = 0.0;
+  for (int sp0 = 0; sp0 < nsplit; sp0 += kRedU) {
+    double v[kRedU];
+#pragma unroll
+    for (int u = 0; u < kRedU; ++u) v[u] = src[(sp0 + u < nsplit ? sp0 + u : nsplit - 1) * step];
+#pragma unroll
+    for (int u = 0; u < kRedU; ++u)
+      if (sp0 + u < nsplit) s += v[u];
   }
+  if (x >= l || y >= l) s = (x == y) ? -1.0 : 0.0;
+  G[(int64_t)x * L + y] = s;
+  G[(int64_t)y * L + x] = s;
+  U[(int64_t)x * L + y] = x == y ? 1.0 : 0.0;
+  U[(int64_t)y * L + x] = x == y ? 1.0 : 0.0;
 }
 
 // aux[0] = kJacAbs * max(0, max_x g_xx): the absolute zero of the sweeps.
@@ -829,7 +843,7 @@ hipError_t launch_wgram2(const RankPlan &P, const float *w, const float *v, int6
                      l, n, P.nt, P.chunk, part);
   hipError_t e = hipGetLastError();
   if (e) return e;
-  hipLaunchKernelGGL(k_wgram_reduce, dim3((unsigned)ntiles), dim3(256), 0, s, part, P.nsplit, P.nt,
+  hipLaunchKernelGGL(k_wgram_reduce, dim3((unsigned)ntiles, 16), dim3(256), 0, s, part, P.nsplit, P.nt,
                      l, (double *)(scr + P.G), (double *)(scr + P.U));
   if ((e = hipGetLastError())) return e;
   hipLaunchKernelGGL(k_jac_floor, dim3(1), dim3(256), 0, s, (const double *)(scr + P.G), P.L,
