@@ -899,8 +899,11 @@ static gcss_status run_jacobi(gcss_ctx *h, const RankPlan &P, char *scr) {
   hipStream_t s = h->stream;
   int conv = 1;
   std::vector<int> flags((size_t)(P.L / 64));
-  for (int sweep = 0; sweep < 30 && conv; ++sweep) {
-    HIPCHK(launch_jacobi_sweep(P, scr, s));
+  // several sweeps between two looks at the flags (a look costs a copy and a
+  // wait, about 20 us; a sweep after the last one needed returns at once)
+  constexpr int kLook = 3;
+  for (int sweep = 0; sweep < 30 && conv;) {
+    for (int x = 0; x < kLook; ++x, ++sweep) HIPCHK(launch_jacobi_sweep(P, scr, sweep == 0, s));
     HIPCHK(hipMemcpyAsync(flags.data(), scr + P.flag, sizeof(int) * flags.size(), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
     conv = 0;

@@ -308,8 +308,9 @@ hipError_t launch_scale_cols(const RankPlan &P, char *scr, const double *u, int6
                              int k, float *b, int64_t ldb, hipStream_t s);
 hipError_t launch_cols_to_f64(const float *in, int64_t ldi, int64_t m, int c, double *out,
                               int64_t ldo, hipStream_t s);
-// one Jacobi sweep; the L / 64 ints at scr + P.flag are all 0 once G is diagonal
-hipError_t launch_jacobi_sweep(const RankPlan &P, char *scr, hipStream_t s);
+// one Jacobi sweep; the L / 64 ints at scr + P.flag are all 0 once G is
+// diagonal, and a sweep other than the first that finds them so does nothing
+hipError_t launch_jacobi_sweep(const RankPlan &P, char *scr, bool first, hipStream_t s);
 // eigenvalue order, sigma, error sums (scr + P.aux + 8: all, tail), then
 // U_A (ua may be null) and V_A (va may be null)
 hipError_t launch_rank_outputs(const RankPlan &P, char *scr, int l, int k, const double *Q,

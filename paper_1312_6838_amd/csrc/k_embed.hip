@@ -41,10 +41,18 @@ hipError_t launch_qless_r(const float *w, int64_t n, int64_t ldw, const int64_t 
 // of 64) with -1 on the padding's diagonal (sorted after every eigenvalue of
 // the positive semidefinite G) and split into 2b blocks of 32 indices.  Each
 // round pairs the blocks by the round-robin (circle) schedule; one workgroup
-// per pair applies a sweep of cyclic Jacobi rotations to its 64 x 64
-// subproblem in LDS, then G <- V^T G V and U <- U V with the block-diagonal V
-// of the round.  A sweep is 2b - 1 rounds; sweeps repeat until every
-// off-diagonal entry is negligible.
+// per pair applies Jacobi rotations to its 64 x 64 subproblem in LDS, then
+// G <- V^T G V and U <- U V with the block-diagonal V of the round.  A sweep
+// is 2b - 1 rounds; sweeps repeat until every off-diagonal entry is
+// negligible.
+//
+// What it costs is the serial chain of inner rounds (32 disjoint rotations
+// each), so a sweep visits every index pair once: its first round rotates all
+// pairs of its subproblems (63 inner rounds), the others only the pairs
+// across their two blocks (32 inner rounds), since pairs inside a block met
+// in the first.  At L = 128 that is 127 inner rounds a sweep instead of 189;
+// the number of sweeps grows by about one (8 -> 9 on a noisy power-law
+// spectrum, counted on the CPU).
 namespace {
 
 constexpr int kJB = 32;       // indices per Jacobi block
@@ -72,9 +80,18 @@ __device__ __forceinline__ int pair_index(int u, int v, int e) {
 
 __device__ __forceinline__ int clamp_idx(int x, int l) { return (x >= 0 && x < l) ? x : 0; }
 
+// (squares of entries of a Gram matrix of binary32 values neither overflow
+// nor vanish)
 __device__ __forceinline__ bool negligible(double gxy, double gxx, double gyy, double fl) {
-  const double a = fabs(gxy);
-  return a <= fl || a <= kJacRel * sqrt(fabs(gxx) * fabs(gyy));
+  return fabs(gxy) <= fl || gxy * gxy <= kJacRel * kJacRel * (fabs(gxx) * fabs(gyy));
+}
+
+// All L / 64 flags of the last check are clear: G is diagonal, nothing to do.
+__device__ __forceinline__ bool jac_done(const int *flag, int L) {
+  if (!flag) return false;
+  int any = 0;
+  for (int b = 0; b < L / 64; ++b) any |= flag[b];
+  return any == 0;
 }
 
 // Partial Gram tiles: workgroup (tile, split) sums W[64a.., c] V[64b.., c]
@@ -184,116 +201,204 @@ __global__ __launch_bounds__(256) void k_jac_floor(const double *__restrict__ G,
   if (threadIdx.x == 0) aux[0] = kJacAbs * fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
 }
 
-// One workgroup per block pair of round r: kJacInner sweeps of cyclic
-// Jacobi on the 64 x 64 subproblem in LDS (one sweep per call is enough for
-// the outer iteration to converge, and costs a quarter of solving each
-// subproblem exactly); writes the rotation V (64 x 64, row-major) to vb[p].
-// A subproblem that is already diagonal is left alone (V = I).  Within an
-// inner round the 32 rotations touch disjoint index pairs, so S <- J^T S J
-// splits into independent 2 x 2 blocks.
-constexpr int kJacInner = 1;
+// One workgroup per block pair of round r: one cycle of Jacobi rotations on
+// the 64 x 64 subproblem in LDS (all its pairs in round 0, else the pairs
+// across the two blocks); writes the rotation V (64 x 64, row-major) to
+// vb[p].  A subproblem that is already diagonal is left alone (V = I).
+// Within an inner round the 32 rotations touch disjoint index pairs, so
+// S <- J^T S J splits into independent 2 x 2 blocks.
+//
+// Bound by the inner rounds' latency and LDS traffic.  1024 threads take one
+// 2 x 2 block of S each; while wave 0 forms the next round's rotations from
+// S, the other waves apply this round's to V, which is kept by columns so
+// that a wave's 64 rows are consecutive words.  The rotation's tangent is
+// taken in binary32 (V only has to be orthogonal, so c and s are normalised
+// in FP64; a tangent off by 1e-7 leaves 1e-7 of the entry, which later
+// rotations see).  An inner round took 1.7 us with 256 threads, the indices
+// in LDS, FP64 roots and divisions and V updated before the next rotations;
+// now 1.2 us (a solve of round 0: 107 -> 81 us, of another round: 43 us).
+constexpr int kJacThreads = 1024;
 
-__global__ __launch_bounds__(256) void k_jac_solve(const double *__restrict__ G, int L, int r,
-                                                   const double *__restrict__ aux,
-                                                   double *__restrict__ vb) {
+__device__ __forceinline__ void jac_inner_pair(bool full, int rr, int p, int &x, int &y) {
+  if (full) {
+    rr_pair(kJP, rr, p, x, y);
+  } else {
+    x = p;
+    y = kJB + ((p + rr) & (kJB - 1));
+  }
+}
+
+// An index of inner pair p, carried from round to round (the modulo of
+// jac_inner_pair for four indices was half of a round's instructions): the
+// index moves by `step` (0: it stays) and wraps from `end` to `start`.
+struct JacIdx {
+  int v, step, end, start;
+  __device__ __forceinline__ void next() {
+    v += step;
+    v = v == end ? start : v;
+  }
+};
+__device__ __forceinline__ void jac_idx(bool full, int p, JacIdx &x, JacIdx &y) {
+  int a, b;
+  jac_inner_pair(full, 0, p, a, b);
+  x = {a, (full && p > 0) ? 1 : 0, kJP - 1, 0};
+  if (x.step == 0) x.end = -1;
+  y = {b, 1, full ? kJP - 1 : kJP, full ? 0 : kJB};
+}
+
+__global__ __launch_bounds__(kJacThreads) void k_jac_solve(const double *__restrict__ G, int L,
+                                                           int r, const double *__restrict__ aux,
+                                                           const int *__restrict__ flag,
+                                                           double *__restrict__ vb) {
   __shared__ double S[kJP][kJLd];
-  __shared__ double V[kJP][kJLd];
-  __shared__ double cs[kJB], sn[kJB];
-  __shared__ int px[kJB], py[kJB];
-  __shared__ int busy, nrot;
+  __shared__ double V[kJP][kJLd];  // V[j][i]: column j of the rotation
+  __shared__ double2 cs[2][kJB];
+  __shared__ int busy, nrot[2];
+  if (jac_done(flag, L)) return;
   const int p = blockIdx.x;
+  const bool full = r == 0;
   int u, v;
   rr_pair(L / kJB, r, p, u, v);
   const double fl = aux[0];
   if (threadIdx.x == 0) busy = 0;
-  for (int e = threadIdx.x; e < kJP * kJP; e += 256) {
+#pragma unroll
+  for (int e = threadIdx.x; e < kJP * kJP; e += kJacThreads) {
     const int i = e / kJP, j = e % kJP;
     S[i][j] = G[(int64_t)pair_index(u, v, i) * L + pair_index(u, v, j)];
-    V[i][j] = i == j ? 1.0 : 0.0;
+    V[j][i] = i == j ? 1.0 : 0.0;
   }
   __syncthreads();
   {
     int mine = 0;
-    for (int e = threadIdx.x; e < kJP * kJP; e += 256) {
+#pragma unroll
+    for (int e = threadIdx.x; e < kJP * kJP; e += kJacThreads) {
       const int i = e / kJP, j = e % kJP;
-      if (i < j && !negligible(S[i][j], S[i][i], S[j][j], fl)) mine = 1;
+      if (i < j && (full || (i < kJB && j >= kJB)) && !negligible(S[i][j], S[i][i], S[j][j], fl)) mine = 1;
     }
     if (mine) busy = 1;  // benign race: every writer stores 1
   }
   __syncthreads();
-  for (int sweep = 0; busy && sweep < kJacInner; ++sweep) {
-    if (threadIdx.x == 0) nrot = 0;
-    for (int rr = 0; rr < kJP - 1; ++rr) {
-      if (threadIdx.x < kJB) {
-        int x, y;
-        rr_pair(kJP, rr, threadIdx.x, x, y);
-        const double gxx = S[x][x], gyy = S[y][y], gxy = S[x][y];
-        double c = 1.0, sv = 0.0;
-        if (!negligible(gxy, gxx, gyy, fl)) {
-          const double tau = (gyy - gxx) / (2.0 * gxy);
-          const double t = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-          c = 1.0 / sqrt(1.0 + t * t);
-          sv = t * c;
-          nrot = 1;  // benign race
-        }
-        cs[threadIdx.x] = c;
-        sn[threadIdx.x] = sv;
-        px[threadIdx.x] = x;
-        py[threadIdx.x] = y;
+  const int nrounds = busy ? (full ? kJP - 1 : kJB) : 0;
+  const int P = threadIdx.x >> 5, Q = threadIdx.x & 31;  // this thread's block of S
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  JacIdx x0, y0, x1, y1, xr, yr;
+  jac_idx(full, P, x0, y0);
+  jac_idx(full, Q, x1, y1);
+  jac_idx(full, Q, xr, yr);
+  // wave 0: the rotations of inner round rr, one pair per lane (pair = lane)
+  auto rotations = [&](int rr) {
+    bool rot = false;
+    if (lane < kJB) {
+      const int x = xr.v, y = yr.v;
+      const double gxx = S[x][x], gyy = S[y][y], gxy = S[x][y];
+      double c = 1.0, sv = 0.0;
+      rot = !negligible(gxy, gxx, gyy, fl);
+      if (rot) {
+        // the smaller root of t^2 + 2 tau t = 1, tau = (gyy - gxx) / (2 gxy);
+        // |tau| < 1e15 (gxy is above kJacAbs max g)
+        const float tau = (float)((gyy - gxx) * __builtin_amdgcn_rcp(2.0 * gxy));
+        const float tf = copysignf(
+            __builtin_amdgcn_rcpf(fabsf(tau) + __builtin_amdgcn_sqrtf(fmaf(tau, tau, 1.f))), tau);
+        const double t = (double)tf, h = fma(t, t, 1.0);
+        // c = h^-1/2: two Newton steps on the hardware's estimate
+        c = __builtin_amdgcn_rsq(h);
+        c = fma(0.5 * c, fma(-h * c, c, 1.0), c);
+        c = fma(0.5 * c, fma(-h * c, c, 1.0), c);
+        sv = t * c;
       }
-      __syncthreads();
-      // S <- J^T S J by 2 x 2 blocks (row pair P, column pair Q)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int blk = e * 256 + threadIdx.x;
-        const int P = blk >> 5, Q = blk & 31;
-        const int x0 = px[P], y0 = py[P], x1 = px[Q], y1 = py[Q];
-        const double cp = cs[P], sp = sn[P], cq = cs[Q], sq = sn[Q];
-        const double a00 = S[x0][x1], a01 = S[x0][y1], a10 = S[y0][x1], a11 = S[y0][y1];
-        const double r00 = cp * a00 - sp * a10, r01 = cp * a01 - sp * a11;
-        const double r10 = sp * a00 + cp * a10, r11 = sp * a01 + cp * a11;
-        double b00 = cq * r00 - sq * r01, b01 = sq * r00 + cq * r01;
-        double b10 = cq * r10 - sq * r11, b11 = sq * r10 + cq * r11;
-        if (P == Q && sp != 0.0) {  // the rotated pair's entry is zero
-          b01 = 0.0;
-          b10 = 0.0;
-        }
-        S[x0][x1] = b00;
-        S[x0][y1] = b01;
-        S[y0][x1] = b10;
-        S[y0][y1] = b11;
-      }
-      // V <- V J: row i, column pair Q
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int t = e * 256 + threadIdx.x;
-        const int Q = t >> 6, i = t & 63;
-        const int x = px[Q], y = py[Q];
-        const double c = cs[Q], sv = sn[Q];
-        const double va = V[i][x], vbv = V[i][y];
-        V[i][x] = c * va - sv * vbv;
-        V[i][y] = sv * va + c * vbv;
-      }
-      __syncthreads();
+      cs[rr & 1][lane] = make_double2(c, sv);
     }
-    if (nrot == 0) break;
+    const bool any = __ballot(rot) != 0;
+    if (lane == 0) nrot[rr & 1] = any;
+    xr.next();
+    yr.next();
+  };
+  if (nrounds && wave == 0) rotations(0);
+  __syncthreads();
+  for (int rr = 0; rr < nrounds; ++rr) {
+    const double2 *const J = cs[rr & 1];
+    const bool any = nrot[rr & 1] != 0;
+    if (any) {
+      // S <- J^T S J by 2 x 2 blocks (row pair P, column pair Q)
+      const double2 cp = J[P], cq = J[Q];
+      double *const sx = S[x0.v], *const sy = S[y0.v];
+      const double a00 = sx[x1.v], a01 = sx[y1.v], a10 = sy[x1.v], a11 = sy[y1.v];
+      const double r00 = cp.x * a00 - cp.y * a10, r01 = cp.x * a01 - cp.y * a11;
+      const double r10 = cp.y * a00 + cp.x * a10, r11 = cp.y * a01 + cp.x * a11;
+      sx[x1.v] = cq.x * r00 - cq.y * r01;
+      sx[y1.v] = cq.y * r00 + cq.x * r01;
+      sy[x1.v] = cq.x * r10 - cq.y * r11;
+      sy[y1.v] = cq.y * r10 + cq.x * r11;
+    }
+    x0.next();
+    y0.next();
+    x1.next();
+    y1.next();
+    __syncthreads();
+    if (wave == 0) {
+      if (rr + 1 < nrounds) rotations(rr + 1);
+    } else if (any) {
+      // V <- V J: one row per lane, pairs wave - 1, wave + 14, ...
+      for (int q = wave - 1; q < kJB; q += kJacThreads / 64 - 1) {
+        int x, y;
+        jac_inner_pair(full, rr, q, x, y);
+        const double2 c = J[q];
+        const double va = V[x][lane], vc = V[y][lane];
+        V[x][lane] = c.x * va - c.y * vc;
+        V[y][lane] = c.y * va + c.x * vc;
+      }
+    }
     __syncthreads();
   }
   double *o = vb + (int64_t)p * kJP * kJP;
-  for (int e = threadIdx.x; e < kJP * kJP; e += 256) o[e] = V[e / kJP][e % kJP];
+#pragma unroll
+  for (int e = threadIdx.x; e < kJP * kJP; e += kJacThreads) o[e] = V[e % kJP][e / kJP];
+}
+
+// 64 x 64 FP64 products on the matrix cores: wave w of 16 forms the 16 x 16
+// tile (w / 4, w % 4) of X Y.  v_mfma_f64_16x16x4: lane l gives row l % 16 of
+// X and column l % 16 of Y at k = l / 16, and register v of the result holds
+// row l / 16 + 4 v, column l % 16.  xt: X[i][k] is read as x[k * ldx + i].
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
+constexpr int kJRow = 68;  // LDS pitch (doubles) of a left operand read by rows
+constexpr int kJCol = 80;  // ... of one read by columns (right, or transposed left)
+
+template <bool XT>
+__device__ __forceinline__ f64x4_t jac_mm(const double *x, const double *y) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int i = (wave >> 2) * 16 + (lane & 15), j = (wave & 3) * 16 + (lane & 15), k0 = lane >> 4;
+  f64x4_t acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int s = 0; s < kJP / 4; ++s) {
+    const int k = 4 * s + k0;
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(XT ? x[k * kJCol + i] : x[i * kJRow + k],
+                                               y[k * kJCol + j], acc, 0, 0, 0);
+  }
+  return acc;
+}
+__device__ __forceinline__ void jac_mm_store(const f64x4_t &acc, double *o, int ld) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int v = 0; v < 4; ++v)
+    o[((wave >> 2) * 16 + (lane >> 4) + 4 * v) * ld + (wave & 3) * 16 + (lane & 15)] = acc[v];
 }
 
 // G <- V^T G V and U <- U V for the block-diagonal V of round r.  The first
 // b(b+1)/2 workgroups take the block-pair regions (p, q), p <= q, of G (and
 // write the mirror); the rest take 64-row slabs of U times a pair's columns.
-__global__ __launch_bounds__(256) void k_jac_apply(double *__restrict__ G, double *__restrict__ U,
-                                                   int L, int r, const double *__restrict__ vb) {
-  __shared__ double X[kJP][kJLd];
-  __shared__ double Vp[kJP][kJLd];
-  __shared__ double Vq[kJP][kJLd];
+// (With 256 threads and vector arithmetic, LDS reads made it 18 us at L = 128;
+// on the matrix cores 8.8 us.)
+__global__ __launch_bounds__(kJacThreads) void k_jac_apply(double *__restrict__ G,
+                                                           double *__restrict__ U, int L, int r,
+                                                           const int *__restrict__ flag,
+                                                           const double *__restrict__ vb) {
+  __shared__ double X[kJP * kJRow];
+  __shared__ double Vp[kJP * kJCol];
+  __shared__ double Vq[kJP * kJCol];
+  if (jac_done(flag, L)) return;
   const int nb = L / kJP;  // pairs
   const int ngg = nb * (nb + 1) / 2;
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
   const int n2 = L / kJB;
   if ((int)blockIdx.x < ngg) {
     int p = 0, rem = blockIdx.x;
@@ -305,106 +410,69 @@ __global__ __launch_bounds__(256) void k_jac_apply(double *__restrict__ G, doubl
     int up, vp, uq, vq;
     rr_pair(n2, r, p, up, vp);
     rr_pair(n2, r, q, uq, vq);
-    for (int e = threadIdx.x; e < kJP * kJP; e += 256) {
+#pragma unroll
+    for (int e = threadIdx.x; e < kJP * kJP; e += kJacThreads) {
       const int i = e / kJP, j = e % kJP;
-      X[i][j] = G[(int64_t)pair_index(up, vp, i) * L + pair_index(uq, vq, j)];
-      Vp[i][j] = vb[(int64_t)p * kJP * kJP + e];
-      Vq[i][j] = vb[(int64_t)q * kJP * kJP + e];
+      X[i * kJRow + j] = G[(int64_t)pair_index(up, vp, i) * L + pair_index(uq, vq, j)];
+      Vp[i * kJCol + j] = vb[(int64_t)p * kJP * kJP + e];
+      Vq[i * kJCol + j] = vb[(int64_t)q * kJP * kJP + e];
     }
     __syncthreads();
-    // T = X Vq (rows 4ty.., columns tx + 16 j)
-    double t[4][4] = {};
-    for (int x = 0; x < kJP; ++x) {
-      double xa[4], vv[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) xa[i] = X[ty * 4 + i][x];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) vv[j] = Vq[x][tx + 16 * j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) t[i][j] = fma(xa[i], vv[j], t[i][j]);
-    }
+    const f64x4_t t = jac_mm<false>(X, Vq);  // T = X Vq
+    __syncthreads();
+    jac_mm_store(t, Vq, kJCol);
+    __syncthreads();
+    jac_mm_store(jac_mm<true>(Vp, Vq), X, kJRow);  // Y = Vp^T T
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) X[ty * 4 + i][tx + 16 * j] = t[i][j];
-    __syncthreads();
-    // Y = Vp^T T
-    double y[4][4] = {};
-    for (int x = 0; x < kJP; ++x) {
-      double va[4], tv[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) va[i] = Vp[x][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) tv[j] = X[x][tx + 16 * j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) y[i][j] = fma(va[i], tv[j], y[i][j]);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) X[ty * 4 + i][tx + 16 * j] = y[i][j];
-    __syncthreads();
-    for (int e = threadIdx.x; e < kJP * kJP; e += 256) {
+    for (int e = threadIdx.x; e < kJP * kJP; e += kJacThreads) {
       const int i = e / kJP, j = e % kJP;
       const int gi = pair_index(up, vp, i), gj = pair_index(uq, vq, j);
       // the diagonal region is kept exactly symmetric
-      const double val = p == q ? 0.5 * (X[i][j] + X[j][i]) : X[i][j];
-      G[(int64_t)gi * L + gj] = val;
-      if (p != q) G[(int64_t)gj * L + gi] = val;
+      G[(int64_t)gi * L + gj] = p == q ? 0.5 * (X[i * kJRow + j] + X[j * kJRow + i]) : X[i * kJRow + j];
+      // (mirror, by its rows)
+      if (p != q)
+        G[(int64_t)pair_index(uq, vq, i) * L + pair_index(up, vp, j)] = X[j * kJRow + i];
     }
   } else {
     const int blk = blockIdx.x - ngg;
     const int rb = blk / nb, p = blk % nb;
     int up, vp;
     rr_pair(n2, r, p, up, vp);
-    for (int e = threadIdx.x; e < kJP * kJP; e += 256) {
+#pragma unroll
+    for (int e = threadIdx.x; e < kJP * kJP; e += kJacThreads) {
       const int i = e / kJP, j = e % kJP;
-      X[i][j] = U[(int64_t)(rb * kJP + i) * L + pair_index(up, vp, j)];
-      Vp[i][j] = vb[(int64_t)p * kJP * kJP + e];
+      X[i * kJRow + j] = U[(int64_t)(rb * kJP + i) * L + pair_index(up, vp, j)];
+      Vp[i * kJCol + j] = vb[(int64_t)p * kJP * kJP + e];
     }
     __syncthreads();
-    double t[4][4] = {};
-    for (int x = 0; x < kJP; ++x) {
-      double xa[4], vv[4];
+    const f64x4_t t = jac_mm<false>(X, Vp);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) xa[i] = X[ty * 4 + i][x];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) vv[j] = Vp[x][tx + 16 * j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) t[i][j] = fma(xa[i], vv[j], t[i][j]);
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        U[(int64_t)(rb * kJP + ty * 4 + i) * L + pair_index(up, vp, tx + 16 * j)] = t[i][j];
+    for (int v = 0; v < 4; ++v)
+      U[(int64_t)(rb * kJP + (wave >> 2) * 16 + (lane >> 4) + 4 * v) * L +
+        pair_index(up, vp, (wave & 3) * 16 + (lane & 15))] = t[v];
   }
 }
 
 // flag[b] = 1 if row slab b (64 rows) of G holds an off-diagonal entry
 // that is not negligible, else 0.
-__global__ __launch_bounds__(256) void k_jac_check(const double *__restrict__ G, int L,
-                                                   const double *__restrict__ aux,
-                                                   int *__restrict__ flag) {
+__global__ __launch_bounds__(kJacThreads) void k_jac_check(const double *__restrict__ G, int L,
+                                                           const double *__restrict__ aux,
+                                                           int *__restrict__ flag) {
   __shared__ int any;
+  __shared__ double diag[kRankMaxL];
   if (threadIdx.x == 0) any = 0;
+  for (int x = threadIdx.x; x < L; x += kJacThreads) diag[x] = G[(int64_t)x * L + x];
   __syncthreads();
   const double fl = aux[0];
   int mine = 0;
   const int x0 = blockIdx.x * 64;
-  for (int e = threadIdx.x; e < 64 * L; e += 256) {
+#pragma unroll 8
+  for (int e = threadIdx.x; e < 64 * L; e += kJacThreads) {
     const int x = x0 + e / L, y = e % L;
-    if (y == x) continue;
     const double gxy = G[(int64_t)x * L + y];
-    if (!negligible(gxy, G[(int64_t)x * L + x], G[(int64_t)y * L + y], fl)) mine = 1;
+    if (y != x && !negligible(gxy, diag[x], diag[y], fl)) mine = 1;
   }
   if (mine) any = 1;  // benign race: every writer stores 1
   __syncthreads();
@@ -851,21 +919,23 @@ hipError_t launch_wgram2(const RankPlan &P, const float *w, const float *v, int6
   return hipGetLastError();
 }
 
-hipError_t launch_jacobi_sweep(const RankPlan &P, char *scr, hipStream_t s) {
+hipError_t launch_jacobi_sweep(const RankPlan &P, char *scr, bool first, hipStream_t s) {
   const int L = P.L;
   const int n2 = L / kJB, nb = L / kJP;
   double *G = (double *)(scr + P.G), *U = (double *)(scr + P.U), *vb = (double *)(scr + P.vb);
   const double *aux = (const double *)(scr + P.aux);
+  int *flag = (int *)(scr + P.flag);
+  const int *seen = first ? nullptr : flag;
   const unsigned napply = (unsigned)(nb * (nb + 1) / 2 + (L / kJP) * nb);
   for (int r = 0; r < n2 - 1; ++r) {
-    hipLaunchKernelGGL(k_jac_solve, dim3((unsigned)nb), dim3(256), 0, s, G, L, r, aux, vb);
+    hipLaunchKernelGGL(k_jac_solve, dim3((unsigned)nb), dim3(kJacThreads), 0, s, G, L, r, aux, seen, vb);
     hipError_t e = hipGetLastError();
     if (e) return e;
-    hipLaunchKernelGGL(k_jac_apply, dim3(napply), dim3(256), 0, s, G, U, L, r, vb);
+    hipLaunchKernelGGL(k_jac_apply, dim3(napply), dim3(kJacThreads), 0, s, G, U, L, r, seen, vb);
     if ((e = hipGetLastError())) return e;
   }
-  hipLaunchKernelGGL(k_jac_check, dim3((unsigned)(L / 64)), dim3(256), 0, s, (const double *)G, L,
-                     aux, (int *)(scr + P.flag));
+  hipLaunchKernelGGL(k_jac_check, dim3((unsigned)(L / 64)), dim3(kJacThreads), 0, s, (const double *)G, L,
+                     aux, flag);
   return hipGetLastError();
 }
 
