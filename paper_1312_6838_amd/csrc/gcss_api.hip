@@ -60,7 +60,9 @@ struct Carve {
 // Offsets of every workspace region for a description (sizes only).
 struct Layout {
   size_t f0, g0, f, g, mask0, mask, part, qpart, npart, Q, e1, e2, w, q64, q32, z32, c1, c2, c3, ups,
-      st, idx, obj, scal, pick, quad, ap64, gram, bexp, V, P, Pn, Pu, scratch, total;
+      st, idx, obj, scal, pick, quad, ap64, gram, bexp, V, P, Pn, Pu, wh, P1, P2, scratch, total;
+  int64_t lp1;     // row stride of P1
+  bool hist;       // the history of omega is kept (wh: k_max x n binary32)
   int64_t lp;      // row stride of the dot partials of the per-step chain
   bool chain;      // the per-step chain kernels fit (their LDS holds r_max + k_max + 1 doubles)
   size_t scratch_bytes;
@@ -91,7 +93,7 @@ EigLayout eig_layout(int64_t m, int64_t ldq, int s, int num_cu) {
   return E;
 }
 
-bool make_layout(const gcss_desc *d, int num_cu, Layout *L) {
+bool make_layout_with(const gcss_desc *d, int num_cu, bool hist, Layout *L) {
   const int64_t m = d->m, n = d->n, k = d->k_max, r = d->r_max;
   L->ldq = ld_for(m);
   L->geo = stream_geometry(m, n, d->a_dtype, num_cu);
@@ -105,7 +107,8 @@ bool make_layout(const gcss_desc *d, int num_cu, Layout *L) {
   L->mask0 = c.take<uint8_t>(n);
   L->mask = c.take<uint8_t>(n);
   L->part = c.take<ArgPart>(std::max(L->geo.grid, 1));
-  L->qpart = c.take<double>(std::max(L->geo.grid, 1));
+  // (with the history, one row per step)
+  L->qpart = c.take<double>((size_t)std::max(L->geo.grid, 1) * (d->self_target ? k : 1));
   L->npart = c.take<double>(1024);
   L->Q = c.take<double>((size_t)L->ldq * (k + 1));
   L->e1 = c.take<double>(L->ldq);
@@ -139,6 +142,14 @@ bool make_layout(const gcss_desc *d, int num_cu, Layout *L) {
   L->P = c.take<double>((size_t)chain_row_blocks(m) * L->lp);
   L->Pn = c.take<double>(chain_row_groups(m));
   L->Pu = c.take<double>(chain_row_groups(m));
+  L->hist = L->chain && hist;
+  L->lp1 = (int64_t)up((size_t)k, 4);
+  if (L->hist) {
+    L->wh = c.take<float>((size_t)k * n);
+    const bool slab = chain_slab_fits(m, 0, (int)k);
+    L->P1 = slab ? c.take<double>((size_t)chain_row_groups(m) * L->lp1) : 0;
+    L->P2 = slab && r > 0 ? c.take<double>((size_t)chain_row_groups(m) * L->lp) : 0;
+  }
   // transient scratch: split-K partials, or the reconstruction-error buffers
   size_t s = 0;
   if (d->self_target) s = std::max(s, gram_scratch_bytes(m, n, L->ldq, num_cu));
@@ -156,6 +167,22 @@ bool make_layout(const gcss_desc *d, int num_cu, Layout *L) {
   L->scratch_bytes = s;
   L->scratch = c.take<uint8_t>(s);
   L->total = up(c.off, 256);
+  return true;
+}
+
+// The chain's history of omega costs 4 k_max n bytes; it is kept while that is
+// at most a quarter of A's own (k_max <= lda * element size / 16) or 16 MiB,
+// so it never dominates what a context needs, and where it does not push a
+// problem out of the static workspace (which takes the same layout as a
+// context, so that both run the same kernels).
+bool make_layout(const gcss_desc *d, int num_cu, Layout *L) {
+  const int64_t hb = 4 * (int64_t)d->k_max * d->n;
+  const bool want = hb <= std::max<int64_t>(d->n * d->lda * dtype_bytes(d->a_dtype) / 4, 16 << 20);
+  if (!make_layout_with(d, num_cu, want, L)) return false;
+  if (L->hist && L->total > (size_t)GCSS_STATIC_SCRATCH_BYTES) {
+    Layout S;
+    if (make_layout_with(d, num_cu, false, &S) && S.total <= (size_t)GCSS_STATIC_SCRATCH_BYTES) *L = S;
+  }
   return true;
 }
 
@@ -256,6 +283,8 @@ struct gcss_ctx {
     sb.advance = advance;
     return sb;
   }
+  // the history of omega that the per-step chain reads
+  float *history() const { return use_chain && L.hist ? at<float>(L.wh) : nullptr; }
   double *F0() const { return at<double>(L.scal); }
   double *err_dev() const { return at<double>(L.scal) + 1; }
 };
@@ -354,6 +383,16 @@ hipError_t enqueue_chain(gcss_ctx *h) {
     ca.r = h->r;
     ca.b_bf16 = h->b_dtype == GCSS_BF16;
   }
+  if (h->L.hist) {
+    ca.wh = h->at<float>(h->L.wh);
+    ca.ldw = h->d.n;
+    ca.A = &h->A;
+    ca.part = h->at<ArgPart>(h->L.part);
+    ca.npart = h->target == 2 ? h->L.geo.grid_ex : h->L.geo.grid;
+    ca.P1 = h->at<double>(h->L.P1);
+    ca.P2 = h->at<double>(h->L.P2);
+    ca.lp1 = h->L.lp1;
+  }
   ca.q64 = h->at<double>(h->L.q64);
   ca.q32 = h->at<float>(h->L.q32);
   ca.z32 = h->at<float>(h->L.z32);
@@ -432,7 +471,8 @@ hipError_t enqueue_step(gcss_ctx *h, bool timed = true) {
                          h->at<double>(h->L.g0), h->at<uint8_t>(h->L.mask),
                          h->at<ArgPart>(h->L.part), h->at<DevState>(h->L.st),
                          h->at<double>(h->L.ap64), 0, ex ? h->at<double>(h->L.qpart) : nullptr,
-                         ex ? h->at<double>(h->L.quad) : nullptr, h->emb, h->ldw, h->stream)))
+                         ex ? h->at<double>(h->L.quad) : nullptr, h->emb, h->ldw, h->history(),
+                         h->history() != nullptr, h->stream)))
     return e;
   if (timed && (e = record(h))) return e;
   return hipSuccess;
@@ -444,7 +484,8 @@ hipError_t enqueue_step(gcss_ctx *h, bool timed = true) {
 hipError_t enqueue_exact_objective(gcss_ctx *h) {
   if (h->target != 2) return hipSuccess;
   const StepBufs sb = h->bufs();
-  return launch_obj_from_quad(h->F0(), h->at<double>(h->L.quad), sb.st, sb.obj, h->stream);
+  return launch_obj_from_quad(h->F0(), h->history() ? h->at<double>(h->L.qpart) : nullptr,
+                              h->L.geo.grid_ex, h->at<double>(h->L.quad), sb.st, sb.obj, h->stream);
 }
 
 hipError_t enqueue_begin(gcss_ctx *h, int k) {
@@ -454,12 +495,15 @@ hipError_t enqueue_begin(gcss_ctx *h, int k) {
                                      h->at<double>(h->L.g), h->at<uint8_t>(h->L.mask), h->d.n, sb,
                                      k, h->d.k_max, h->F0(), h->d.tau, h->stream);
   if (e) return e;
-  // first argmax over the initial scores
+  // first argmax over the initial scores (with the history, by the kernel of
+  // the loop's passes, so that as many winners are written as the chain reads)
+  const bool hist = h->history() != nullptr;
   return launch_stream(h->L.geo, h->A, h->at<float>(h->L.q32), h->at<double>(h->L.q64),
                        h->at<float>(h->L.z32), h->at<double>(h->L.f), h->at<double>(h->L.g),
                        h->at<double>(h->L.g0), h->at<uint8_t>(h->L.mask),
-                       h->at<ArgPart>(h->L.part), sb.st, h->at<double>(h->L.ap64), 1, nullptr,
-                       nullptr, nullptr, 0, h->stream);
+                       h->at<ArgPart>(h->L.part), sb.st, h->at<double>(h->L.ap64), 1,
+                       hist && h->target == 2 ? h->at<double>(h->L.qpart) : nullptr, nullptr,
+                       nullptr, 0, nullptr, hist, h->stream);
 }
 
 // Begin + k + kSpareSlots steps + the exact objective (and, with finish, the

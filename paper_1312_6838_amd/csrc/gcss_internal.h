@@ -76,12 +76,16 @@ StreamGeo stream_geometry(int64_t m, int64_t n, int dtype, int num_cu);
 hipError_t stream_finalize(StreamGeo &geo, int64_t n, int dtype, int num_cu);
 // qpart/quad non-null: the exact-decrease variant (Gram target), which reads
 // q64 and writes sum_i (A_i . q)^2 to quad[t - 1].  emb non-null: row t - 1
-// of the row-major embedding W (leading dimension ldw) receives A_i . q.
+// of the row-major embedding W (leading dimension ldw) receives A_i . q; wh
+// non-null: row t - 1 of the history (leading dimension n) does too, and the
+// pass leaves its winners (and, with qpart, row t - 1 of the per-workgroup
+// sums, grid_ex long) to the chain and the final objective: no next pick is
+// written, ap64 and quad are not used.  defer: the same for a score-only pass.
 hipError_t launch_stream(const StreamGeo &geo, const AView &A, const float *q32,
                          const double *q64, const float *z32, double *f, double *g,
                          const double *g0, uint8_t *mask, ArgPart *part, DevState *st,
                          double *ap64, int score_only, double *qpart, double *quad,
-                         float *emb, int64_t ldw, hipStream_t s);
+                         float *emb, int64_t ldw, float *wh, bool defer, hipStream_t s);
 
 // ---- launchers (k_gemv.hip) ----
 // Buffers of one selection problem that the per-step kernels touch.
@@ -191,6 +195,17 @@ struct ChainArgs {
   double *P;          // dot partials: row blocks x lp
   int64_t lp;         // >= r + kmax + 1 (B = A: m + kmax + 1)
   double *Pn, *Pu;    // one double per row workgroup each
+  // history of omega (row s: A^T q_{s+1} in binary32, ld ldw), or null; with
+  // it the chain takes the pick from the streaming pass's npart winners and
+  // decodes its column of A (`a` is not read), and the slab form's partials
+  // are P1 (row workgroups x lp1 >= kmax) and P2 (x lp)
+  const float *wh;
+  int64_t ldw;
+  const ArgPart *part;
+  int npart;
+  const AView *A;
+  double *P1, *P2;
+  int64_t lp1;
   const void *B;      // explicit target (binary32 or bfloat16), or C = A A^T (binary32)
   int64_t ldb;
   int64_t r;          // target width (0 for B = A)
@@ -220,6 +235,8 @@ int chain_row_groups(int64_t m);
 size_t chain_lds_bytes(int64_t r, int kmax);
 // the chain serves the shape: m within its row blocks, r + kmax + 1 doubles of LDS
 bool chain_fits(int64_t m, int64_t r, int kmax, size_t lds_max);
+// the slab form serves the shape (with the history of omega; r = 0: B = A)
+bool chain_slab_fits(int64_t m, int64_t r, int kmax);
 hipError_t launch_chain(const ChainArgs &ca, hipStream_t s);
 // The same step with one workgroup per problem (small problems: m <= 2048,
 // explicit target; ca.nprob problems at the strides of ChainArgs)
@@ -248,9 +265,10 @@ hipError_t launch_project(const AView &A, const float *omega, int64_t r, float *
 size_t qta_scratch_bytes(int64_t n, int kmax);
 hipError_t launch_qta(const double *Q, int64_t ldq, int kmax, const DevState *st,
                       const AView &A, double *scratch, double *quad, hipStream_t s);
-// obj[s+1] = F0 - sum_{x<=s} quad[x], s < st->t
-hipError_t launch_obj_from_quad(const double *F0, const double *quad, const DevState *st,
-                                double *obj, hipStream_t s);
+// obj[s+1] = F0 - sum_{x<=s} quad[x], s < st->t; qpart given: first quad[s] =
+// the sum of qpart's row s (nq entries)
+hipError_t launch_obj_from_quad(const double *F0, const double *qpart, int nq, double *quad,
+                                const DevState *st, double *obj, hipStream_t s);
 
 // ---- launchers (k_quant.hip) ----
 hipError_t launch_quantize(const float *a, int64_t m, int64_t n, int64_t lda, int dtype,

@@ -24,6 +24,25 @@
 // (equal to Q^T w, since q_s^T B B^T q = w_s^T q), so it needs no reduction
 // after w is known.
 //
+// With the history of the streaming passes' omega (wh, row s holds A^T q_{s+1}
+// in binary32, so c1 = column p of it) the first reduction is already done,
+// and a workgroup of 32 rows that holds its rows of Q can do a row update and
+// the partial dots after it in one go:
+//
+//   S1  e1 = a - Q c1 (a decoded from column p of A),  partials of Q^T e1
+//   S2  e2 = e1 - Q c2, ||e2||^2,  partials of [B^T e2 ; V^T e2]
+//   S3  = K6 on partials per 32 rows                   (B = A: K5, then K6)
+//
+// c1 is off by binary32 rounding (1e-7 ||a||); the second projection, formed
+// in FP64 from e1 as it is, takes that out with the rest of Q's span, so e2 is
+// orthogonal to Q to FP64 rounding of ||e1|| as before.  The partials of a
+// consumer grow with m (m / 32 rows of r + t), so this form serves shapes
+// whose partials stay small; above, S1 without partials replaces K1 and K2.
+// The chain's kernel time per step on MI355X, six kernels -> now: m = 1024,
+// r = 128, k = 50: 29 -> 19 us; m = 3001, r = 200, k = 64: 33 -> 23 us; m = 4096,
+// B = A, k = 200: 42 -> 37 us; m = 8192, r = 512, k = 500 (no slab): 44 -> 40 us;
+// the streaming pass without its last workgroup's work takes 7 us less.
+//
 // Latency is what these kernels spend: each one reads the device state, then
 // issues every load it needs at once (partials of the previous kernel, the
 // rows of Q, B or V it multiplies), so a kernel costs about two memory round
@@ -33,6 +52,8 @@
 // workgroup of 1024 threads owns 32 rows and its 32 groups of 32 lanes split
 // the sum over columns; partial sums meet in LDS in a fixed order.  Every
 // reduction has a fixed order, so results do not depend on scheduling.
+#include <type_traits>
+
 #include "gcss_device.h"
 
 namespace gcss {
@@ -43,7 +64,11 @@ constexpr int kMaxRB = 8;       // row blocks of the dot kernels (m <= 8192)
 constexpr int kRowRB = 32;      // rows per row-kernel workgroup
 constexpr int kRowGroups = 32;  // column groups per row-kernel workgroup
 constexpr int kRowThreads = kRowRB * kRowGroups;  // 1024
-constexpr int kRowU = 16;       // columns per thread loaded in one round (t <= 512: one round)
+// columns per thread loaded in one round: the smallest U of 4, 8, 16 that takes
+// a matrix in one round (32 U columns), the largest with further rounds.  A
+// thread issues U loads (clamped) whatever the column count, so U = 16 for 20
+// columns costs most of a row kernel's issue slots.
+constexpr int kRowUMax = 16;
 
 template <typename T>
 __device__ __forceinline__ double to_f64(T v) {
@@ -198,41 +223,41 @@ __global__ __launch_bounds__(256) void k_dots(const T1 *__restrict__ M1, int64_t
 }
 
 // Loads of one round of a thread's row sum: M[j + s ld] for the columns
-// s = s0 + 32 u (u < kRowU), raw, all issued before any is used; a column
+// s = s0 + 32 u (u < U), raw, all issued before any is used; a column
 // s >= ns reads column ns - 1 instead, and is dropped by the caller (ns <= 0:
 // nothing is read).
-template <typename T>
+template <typename T, int U>
 __device__ __forceinline__ void row_loads(const T *__restrict__ col0, int64_t ld, int s0, int ns,
-                                          T (&raw)[kRowU]) {
+                                          T (&raw)[U]) {
   if (ns <= 0) {  // (the same in the whole workgroup)
 #pragma unroll
-    for (int u = 0; u < kRowU; ++u) raw[u] = T(0);
+    for (int u = 0; u < U; ++u) raw[u] = T(0);
     return;
   }
 #pragma unroll
-  for (int u = 0; u < kRowU; ++u) {
+  for (int u = 0; u < U; ++u) {
     const int s = s0 + kRowGroups * u;
     raw[u] = col0[(int64_t)(s < ns ? s : ns - 1) * ld];
   }
 }
 
 // The row sum of one thread: sum over columns s = g, g + 32, ... < ns of
-// M[j + s ld] * c[s], the first kRowU terms from preloaded values, the rest
-// (ns > 32 kRowU) loaded in further rounds.
-template <typename T>
+// M[j + s ld] * c[s], the first U terms from preloaded values, the rest
+// (ns > 32 U) loaded in further rounds.
+template <typename T, int U>
 __device__ __forceinline__ double row_sum(const T *__restrict__ col0, int64_t ld, int g, int ns,
-                                          const double (&pre)[kRowU], const double *c) {
+                                          const double (&pre)[U], const double *c) {
   double acc = 0.0;
 #pragma unroll
-  for (int u = 0; u < kRowU; ++u) {
+  for (int u = 0; u < U; ++u) {
     const int s = g + kRowGroups * u;
     if (s < ns) acc = fma(pre[u], c[s], acc);
   }
-  for (int s0 = g + kRowGroups * kRowU; s0 < ns; s0 += kRowGroups * kRowU) {
-    T raw[kRowU];
+  for (int s0 = g + kRowGroups * U; s0 < ns; s0 += kRowGroups * U) {
+    T raw[U];
     row_loads(col0, ld, s0, ns, raw);
 #pragma unroll
-    for (int u = 0; u < kRowU; ++u) {
+    for (int u = 0; u < U; ++u) {
       const int s = s0 + kRowGroups * u;
       if (s < ns) acc = fma(to_f64(raw[u]), c[s], acc);
     }
@@ -240,26 +265,36 @@ __device__ __forceinline__ double row_sum(const T *__restrict__ col0, int64_t ld
   return acc;
 }
 
-// The first kRowU values of a thread's row sum (columns g + 32 u < ns; the
+// The first U values of a thread's row sum (columns g + 32 u < ns; the
 // others 0).  The loads are unconditional (clamped columns), so they are all
 // in flight together instead of each waited for inside its own branch.
-template <typename T>
-__device__ __forceinline__ void row_convert(const T (&raw)[kRowU], int g, int ns,
-                                            double (&pre)[kRowU]) {
+template <typename T, int U>
+__device__ __forceinline__ void row_convert(const T (&raw)[U], int g, int ns,
+                                            double (&pre)[U]) {
 #pragma unroll
-  for (int u = 0; u < kRowU; ++u) pre[u] = g + kRowGroups * u < ns ? to_f64(raw[u]) : 0.0;
+  for (int u = 0; u < U; ++u) pre[u] = g + kRowGroups * u < ns ? to_f64(raw[u]) : 0.0;
 }
-template <typename T>
+template <typename T, int U>
 __device__ __forceinline__ void row_preload(const T *__restrict__ col0, int64_t ld, int g, int ns,
-                                            double (&pre)[kRowU]) {
-  T raw[kRowU];
+                                            double (&pre)[U]) {
+  T raw[U];
   row_loads(col0, ld, g, ns, raw);
   row_convert(raw, g, ns, pre);
 }
 
+// The rows' sums over the 32 column groups, by wave 0: lanes 0..31 add groups
+// 0..15 of their row, lanes 32..63 the rest.
+__device__ __forceinline__ double row_total(const double (*red)[kRowRB + 1]) {
+  const int r = threadIdx.x & (kRowRB - 1), x0 = (threadIdx.x >> 5) * (kRowGroups / 2);
+  double s = 0.0;
+#pragma unroll
+  for (int x = 0; x < kRowGroups / 2; ++x) s += red[x0 + x][r];
+  return s + __shfl_xor(s, 32, 64);
+}
+
 // out = v - Q c for this workgroup's 32 rows, c[s] = sum_y P[y * lp + s]
 // (s < t); NORM: Pn[blockIdx.x] = sum of out^2 over its rows.
-template <bool NORM>
+template <bool NORM, int UQ>
 __global__ __launch_bounds__(1024) void k_rows_sub(const double *__restrict__ Q, int64_t ldq,
                                                    const double *__restrict__ v,
                                                    const double *__restrict__ P, int64_t lp,
@@ -284,7 +319,7 @@ __global__ __launch_bounds__(1024) void k_rows_sub(const double *__restrict__ Q,
   const int64_t j = (int64_t)blockIdx.x * kRowRB + r;
   const int64_t jc = j < m ? j : m - 1;
   // loads: this thread's first columns of Q, the base value, the coefficients
-  double pre[kRowU];
+  double pre[UQ];
   row_preload(Q + jc, ldq, g, t, pre);
   const double vj = v[jc];
   for (int s = threadIdx.x; s < t; s += kRowThreads) cs[s] = psum(P, lp, nrb, s);
@@ -292,10 +327,9 @@ __global__ __launch_bounds__(1024) void k_rows_sub(const double *__restrict__ Q,
   red[g][r] = row_sum(Q + jc, ldq, g, t, pre, cs);
   __syncthreads();
   if (threadIdx.x < 64) {  // wave 0: lanes 0..31 own the rows
+    const double sum = row_total(red);
     double o = 0.0;
     if (threadIdx.x < kRowRB && j < m) {
-      double sum = 0.0;
-      for (int x = 0; x < kRowGroups; ++x) sum += red[x][r];
       o = vj - sum;
       out[j] = o;
     }
@@ -303,6 +337,223 @@ __global__ __launch_bounds__(1024) void k_rows_sub(const double *__restrict__ Q,
       const double sq = wave_sum(o * o);
       if (threadIdx.x == 0) Pn[blockIdx.x] = sq;
     }
+  }
+}
+
+// ---- the slab form (S1, S2; see the file comment) ----
+
+// Sum over each half of a wave (32 lanes), in lanes 31 and 63: four DPP steps
+// leave a row's sum in its 16 lanes, one row broadcast adds row 0 to row 1
+// and row 2 to row 3.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ double dpp_step64(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROW_MASK, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROW_MASK, 0xF, false);
+  return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double half_total(double v) {
+  v += dpp_step64<0xB1, 0xF>(v);   // quad_perm [1,0,3,2]
+  v += dpp_step64<0x4E, 0xF>(v);   // quad_perm [2,3,0,1]
+  v += dpp_step64<0x141, 0xF>(v);  // row_half_mirror
+  v += dpp_step64<0x140, 0xF>(v);  // row_mirror
+  v += dpp_step64<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
+  return v;
+}
+
+// P[s] = sum over the workgroup's 32 rows of x[u] * er for the columns
+// s = g + 32 u < ns (x[u] = 0 beyond ns; er: this lane's row).
+template <int U>
+__device__ __forceinline__ void slab_dots(const double (&x)[U], double er, int g, int ns,
+                                          double *__restrict__ P) {
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    if (kRowGroups * u >= ns) break;
+    const double d = half_total(x[u] * er);
+    const int s = g + kRowGroups * u;
+    if ((threadIdx.x & 31) == 31 && s < ns) P[s] = d;
+  }
+}
+
+// out[c] = sum over y < ng (in a fixed order) of P[y * lp + c], c < ne, by the
+// 1024 threads of a workgroup: with few entries several threads share one,
+// each adding a run of the partials, 16 in flight.  Ends with a barrier.
+__device__ __forceinline__ void slab_sums(const double *__restrict__ P, int64_t lp, int ng, int ne,
+                                          double *out, double *tmp) {
+  int sh = 6;
+  while (sh < 10 && (1 << sh) < ne) ++sh;
+  const int width = 1 << sh, parts = kRowThreads >> sh;
+  const int per = (ng + parts - 1) / parts;
+  const int h = threadIdx.x >> sh, ci = threadIdx.x & (width - 1);
+  const int y0 = h * per, y1 = y0 + per < ng ? y0 + per : ng;
+  for (int c0 = 0; c0 < ne; c0 += width) {
+    const int c = c0 + ci < ne ? c0 + ci : ne - 1;
+    double a = 0.0;
+    for (int y = y0; y < y1; y += 16) {
+      double v[16];
+#pragma unroll
+      for (int x = 0; x < 16; ++x) v[x] = P[(int64_t)(y + x < y1 ? y + x : y1 - 1) * lp + c];
+#pragma unroll
+      for (int x = 0; x < 16; ++x)
+        if (y + x < y1) a += v[x];
+    }
+    if (parts == 1) {
+      if (c0 + ci < ne) out[c0 + ci] = a;
+    } else {
+      tmp[threadIdx.x] = a;
+      __syncthreads();
+      if ((int)threadIdx.x < width && c0 + ci < ne) {
+        double b = 0.0;
+        for (int x = 0; x < parts; ++x) b += tmp[x * width + ci];
+        out[c0 + ci] = b;
+      }
+      __syncthreads();
+    }
+  }
+  __syncthreads();
+}
+
+// S1: the next pick p from the streaming pass's per-workgroup winners (every
+// workgroup reduces them by itself: 256 entries cost less than the pass's last
+// workgroup doing it behind a device-wide arrival), then e1 = a - Q c1 for
+// this workgroup's 32 rows; PART: P[blockIdx.x] = partials of Q^T e1
+// (t <= 32 UQ).  Workgroup 0 writes the pick to the state, whose fields that
+// the other workgroups read here (done, t) change only where none is left.
+template <bool PART, int UQ>
+__global__ __launch_bounds__(1024) void k_gs1(AView A, const float *__restrict__ wh, int64_t ldw,
+                                              const ArgPart *__restrict__ part, int npart,
+                                              const double *__restrict__ Q, int64_t ldq,
+                                              double *__restrict__ e1, double *__restrict__ P,
+                                              int64_t lp, int64_t m, DevState *st) {
+  extern __shared__ double cs[];  // t coefficients
+  __shared__ double red[kRowGroups][kRowRB + 1];
+  __shared__ double er[kRowRB];
+  __shared__ double bs[kRowThreads / 64];
+  __shared__ int64_t bi[kRowThreads / 64];
+  const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+  if (st->done) {
+    if (first) st->dec_pending = 0;  // the pass after the last pick has run
+    return;
+  }
+  const int t = st->t;
+  const int r = threadIdx.x & (kRowRB - 1), g = threadIdx.x / kRowRB;
+  const int64_t j = (int64_t)blockIdx.x * kRowRB + r;
+  const int64_t jc = j < m ? j : m - 1;
+  double raw[UQ], pre[UQ];
+  row_loads(Q + jc, ldq, g, t, raw);
+  double best = -INFINITY;
+  int64_t p = kNoIdx;
+  for (int x = threadIdx.x; x < npart; x += kRowThreads) {
+    const double sc = part[x].score;
+    const int64_t i = part[x].idx;
+    if (better(sc, i, best, p)) {
+      best = sc;
+      p = i;
+    }
+  }
+  const int nw = npart < kRowThreads ? (npart + 63) >> 6 : kRowThreads / 64;
+  if ((int)(threadIdx.x >> 6) < nw) {
+    wave_argmax(best, p);
+    if ((threadIdx.x & 63) == 0) {
+      bs[threadIdx.x >> 6] = best;
+      bi[threadIdx.x >> 6] = p;
+    }
+  }
+  __syncthreads();
+  best = bs[0];
+  p = bi[0];
+  for (int x = 1; x < nw; ++x)
+    if (better(bs[x], bi[x], best, p)) {
+      best = bs[x];
+      p = bi[x];
+    }
+  if (first) {
+    st->skip = 0;
+    st->dec_pending = 0;
+    if (p == kNoIdx) {
+      st->p = -1;
+      st->exhausted = 1;
+      st->done = 1;
+    } else {
+      st->p = p;
+    }
+  }
+  if (p == kNoIdx) return;
+  double aj = 0.0;
+  if (threadIdx.x < kRowRB) aj = col_scale(A, p) * (double)load_elem(A, p, jc);
+  for (int s = threadIdx.x; s < t; s += kRowThreads) cs[s] = (double)wh[(int64_t)s * ldw + p];
+  __syncthreads();
+  row_convert(raw, g, t, pre);
+  red[g][r] = row_sum(Q + jc, ldq, g, t, pre, cs);
+  __syncthreads();
+  if (threadIdx.x < 64) {
+    const double sum = row_total(red);
+    if (threadIdx.x < kRowRB) {
+      const double o = aj - sum;
+      if (j < m) e1[j] = o;
+      if constexpr (PART) er[r] = j < m ? o : 0.0;
+    }
+  }
+  if constexpr (PART) {
+    __syncthreads();
+    slab_dots(pre, er[r], g, t, P + (int64_t)blockIdx.x * lp);
+  }
+}
+
+// S2: e2 = e1 - Q c2 with c2 the sums of S1's partials, the norm partial, and
+// (explicit target) the partials [B^T e2 ; V^T e2] of this workgroup's rows.
+template <typename TB, bool GRAM, int UQ, int UB>
+__global__ __launch_bounds__(1024) void k_gs2(const double *__restrict__ Q, int64_t ldq,
+                                              const double *__restrict__ V,
+                                              const TB *__restrict__ B, int64_t ldb, int r,
+                                              const double *__restrict__ e1,
+                                              const double *__restrict__ P1, int64_t lp1,
+                                              double *__restrict__ e2, double *__restrict__ Pn,
+                                              double *__restrict__ P2, int64_t lp2, int64_t m,
+                                              const DevState *st) {
+  extern __shared__ double cs[];  // t coefficients
+  __shared__ double red[kRowGroups][kRowRB + 1];
+  __shared__ double tmp[kRowThreads];
+  __shared__ double er[kRowRB];
+  if (st->done || st->skip) return;
+  const int t = st->t;
+  const int rr = threadIdx.x & (kRowRB - 1), g = threadIdx.x / kRowRB;
+  const int64_t j = (int64_t)blockIdx.x * kRowRB + rr;
+  const int64_t jc = j < m ? j : m - 1;
+  double qraw[UQ], vraw[UQ];
+  TB braw[UB];
+  row_loads(Q + jc, ldq, g, t, qraw);
+  const double ej = e1[jc];
+  if constexpr (!GRAM) {
+    row_loads(B + jc, ldb, g, r, braw);
+    row_loads(V + jc, ldq, g, t, vraw);
+  }
+  slab_sums(P1, lp1, (int)gridDim.x, t, cs, tmp);
+  double pre[UQ];
+  row_convert(qraw, g, t, pre);
+  red[g][rr] = row_sum(Q + jc, ldq, g, t, pre, cs);
+  __syncthreads();
+  if (threadIdx.x < 64) {  // wave 0: lanes 0..31 own the rows
+    const double sum = row_total(red);
+    double o = 0.0;
+    if (threadIdx.x < kRowRB) {
+      if (j < m) {
+        o = ej - sum;
+        e2[j] = o;
+      }
+      er[rr] = o;
+    }
+    const double sq = wave_sum(o * o);
+    if (threadIdx.x == 0) Pn[blockIdx.x] = sq;
+  }
+  if constexpr (!GRAM) {
+    __syncthreads();
+    const double e = er[rr];
+    double *const P = P2 + (int64_t)blockIdx.x * lp2;
+    double bpre[UB];
+    row_convert(braw, g, r, bpre);
+    slab_dots(bpre, e, g, r, P);
+    row_convert(vraw, g, t, pre);
+    slab_dots(pre, e, g, t, P + r);
   }
 }
 
@@ -333,10 +584,12 @@ struct ZArgs {
 };
 
 // TB: element type of the explicit target (float or bfloat16 bits); GRAM:
-// B = A through C = A A^T (w comes from K5's partials of C e2).
-template <typename TB, bool GRAM>
+// B = A through C = A A^T (w comes from K5's partials of C e2); SLAB: the
+// partials are S2's, one row of r + t per 32-row workgroup.
+template <typename TB, bool GRAM, bool SLAB, int UQ, int UB>
 __global__ __launch_bounds__(1024) void k_rows_z(ZArgs za, DevState *st) {
   extern __shared__ double sh[];  // upsilon (r) then c3 (t)
+  __shared__ double tmp[SLAB ? kRowThreads : 1];
   __shared__ double redw[kRowGroups][kRowRB + 1];
   __shared__ double redz[kRowGroups][kRowRB + 1];
   __shared__ double wsum[kRowThreads / 64];
@@ -368,28 +621,45 @@ __global__ __launch_bounds__(1024) void k_rows_z(ZArgs za, DevState *st) {
   const int64_t jc = j < m ? j : m - 1;
   // every load of the kernel at once: rows of B and Q (kept raw until the
   // row sums), e2, the norm partials, the coefficient partials
-  TB braw[kRowU];
-  double qraw[kRowU];
+  TB braw[UB];
+  double qraw[UQ];
   row_loads(za.Q + jc, za.ldq, g, t, qraw);
   if constexpr (!GRAM) row_loads((const TB *)za.B + jc, za.ldb, g, r, braw);
   const double e2j = za.e2[jc];
+  // ||e2||^2 in a fixed order, by every wave (the same in every workgroup)
   double pn = 0.0;
-  for (int x = threadIdx.x; x < za.npn; x += kRowThreads) pn += za.Pn[x];
+  for (int x = threadIdx.x & 63; x < za.npn; x += 64) pn += za.Pn[x];
   double *ups = sh, *c3 = sh + r;
-  for (int c = threadIdx.x; c < r; c += kRowThreads) ups[c] = psum(za.P, za.lp, za.nrb, c);
-  for (int s = threadIdx.x; s < t; s += kRowThreads) c3[s] = psum(za.P, za.lp, za.nrb, za.nfix + s);
+  if constexpr (SLAB) {
+    slab_sums(za.P, za.lp, (int)gridDim.x, r + t, sh, tmp);
+  } else {
+    for (int c = threadIdx.x; c < r; c += kRowThreads) ups[c] = psum(za.P, za.lp, za.nrb, c);
+    for (int s = threadIdx.x; s < t; s += kRowThreads) c3[s] = psum(za.P, za.lp, za.nrb, za.nfix + s);
+  }
   if constexpr (GRAM)
     if (threadIdx.x < kRowRB) wrow[threadIdx.x] = psum(za.P, za.lp, za.nrb, jc);
-  // ||e2||^2 in a fixed order (the same in every workgroup)
-  const double nrm2 = block_sum(pn, wsum);
+  const double nrm2 = wave_sum(pn);
+  __syncthreads();
+  // Explicit target: the workgroup that arrives here last knows that all have
+  // read the state, so it is the one that will change it; it arrives before
+  // its sums, which hide the atomic.  (B = A needs every workgroup's q . w
+  // partial, so there the last one to finish does.)
+  constexpr int kRec = 64;  // the recording thread: wave 1's first
+  uint32_t prev = 0;
+  if constexpr (!GRAM)
+    if (threadIdx.x == kRec)
+      prev = __hip_atomic_fetch_add(&st->cnt[4], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   // the basis check: a pick whose exact residual is at most tau * g0_p is
   // dropped (every workgroup takes the same decision from the same sum)
   if (!(isfinite(nrm2) && nrm2 > thr)) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    const bool rec = GRAM ? blockIdx.x == 0 && threadIdx.x == 0
+                          : threadIdx.x == kRec && prev == gridDim.x - 1;
+    if (rec) {
       za.mask[p] = 2;
       st->skip = 1;
       st->n_reject += 1;
       st->enorm2 = nrm2;
+      if constexpr (!GRAM) st->cnt[4] = 0;
     }
     return;
   }
@@ -398,7 +668,7 @@ __global__ __launch_bounds__(1024) void k_rows_z(ZArgs za, DevState *st) {
   for (int s = threadIdx.x; s < t; s += kRowThreads) c3[s] *= inv;
   __syncthreads();
   // w = B upsilon and Q c3 for this workgroup's rows
-  double bpre[kRowU], qpre[kRowU];
+  double bpre[UB], qpre[UQ];
   if constexpr (!GRAM) {
     row_convert(braw, g, r, bpre);
     redw[g][rr] = row_sum((const TB *)za.B + jc, za.ldb, g, r, bpre, ups);
@@ -407,16 +677,11 @@ __global__ __launch_bounds__(1024) void k_rows_z(ZArgs za, DevState *st) {
   redz[g][rr] = row_sum(za.Q + jc, za.ldq, g, t, qpre, c3);
   __syncthreads();
   if (threadIdx.x < 64) {
-    double qw = 0.0;
+    double qw = 0.0, wj;
+    const double qc = row_total(redz);
+    if constexpr (GRAM) wj = wrow[rr] * inv;
+    else wj = row_total(redw);
     if (threadIdx.x < kRowRB && j < m) {
-      double wj, qc = 0.0;
-      if constexpr (GRAM) {
-        wj = wrow[rr] * inv;
-      } else {
-        wj = 0.0;
-        for (int x = 0; x < kRowGroups; ++x) wj += redw[x][rr];
-      }
-      for (int x = 0; x < kRowGroups; ++x) qc += redz[x][rr];
       const double qv = e2j * inv;
       za.Q[(int64_t)t * za.ldq + j] = qv;
       za.q64[j] = qv;
@@ -430,20 +695,24 @@ __global__ __launch_bounds__(1024) void k_rows_z(ZArgs za, DevState *st) {
       if (threadIdx.x == 0) za.Pu[blockIdx.x] = sq;
     }
   }
-  // the last workgroup records the pick
-  if (!last_block_arrive(&st->cnt[4])) return;
-  double u2;
+  double u2 = 0.0;
+  bool rec;
   if constexpr (GRAM) {
-    // q . w over all workgroups (visible after last_block_arrive)
+    // the last workgroup records the pick: q . w over all workgroups
+    // (visible after last_block_arrive)
+    if (!last_block_arrive(&st->cnt[4])) return;
     double a = 0.0;
     for (int x = threadIdx.x; x < (int)gridDim.x; x += kRowThreads) a += za.Pu[x];
     u2 = block_sum(a, wsum);
+    rec = threadIdx.x == 0;
   } else {
+    if (threadIdx.x < kRec || threadIdx.x >= kRec + 64) return;
     double a = 0.0;
-    for (int c = threadIdx.x; c < r; c += kRowThreads) a = fma(ups[c], ups[c], a);
-    u2 = block_sum(a, wsum);
+    for (int c = threadIdx.x - kRec; c < r; c += 64) a = fma(ups[c], ups[c], a);
+    u2 = wave_sum(a);
+    rec = threadIdx.x == kRec && prev == gridDim.x - 1;
   }
-  if (threadIdx.x == 0) {
+  if (rec) {
     const double F = st->F - u2;
     st->u2 = u2;
     st->enorm2 = nrm2;
@@ -648,6 +917,25 @@ bool chain_fits(int64_t m, int64_t r, int kmax, size_t lds_max) {
   return chain_row_blocks(m) <= kMaxRB && chain_lds_bytes(r, kmax) <= lds_max;
 }
 
+// The slab form holds one round of a thread's columns (t, r <= 32 kRowUMax), and
+// every workgroup of a consumer reads all partials: m / 32 rows of t (S2) and
+// of r + t (K6).  At 94 x 264 doubles (198 KB; m = 3001) S2 and K6 take 7.8 and
+// 10.2 us against 4.4 + 4.6 + 4.4 + 10.2 us for K3, K4, K5 and K6; each further
+// 100 KB costs them about 1 us, so the line lies near 400 KB.
+constexpr int64_t kSlabBytes = 384 * 1024;
+bool chain_slab_fits(int64_t m, int64_t r, int kmax) {
+  return kmax <= kRowGroups * kRowUMax && r <= kRowGroups * kRowUMax &&
+         (int64_t)chain_row_groups(m) * (r + kmax) * (int64_t)sizeof(double) <= kSlabBytes;
+}
+
+// f(U) with U the smallest of 4, 8, 16 that holds n columns in one round
+template <typename F>
+static void with_row_u(int64_t n, F f) {
+  if (n <= 4 * kRowGroups) f(std::integral_constant<int, 4>{});
+  else if (n <= 8 * kRowGroups) f(std::integral_constant<int, 8>{});
+  else f(std::integral_constant<int, kRowUMax>{});
+}
+
 hipError_t launch_chain(const ChainArgs &ca, hipStream_t s) {
   const int64_t m = ca.m;
   const int nrb = chain_row_blocks(m), nrg = chain_row_groups(m);
@@ -655,40 +943,72 @@ hipError_t launch_chain(const ChainArgs &ca, hipStream_t s) {
   const unsigned qdots = (unsigned)dots_col_blocks(0, ca.kmax);
   const size_t lds_t = (size_t)(ca.kmax + 1) * sizeof(double);
   const unsigned np = (unsigned)(ca.nprob > 0 ? ca.nprob : 1);
-  // K1: c1 partials
-  hipLaunchKernelGGL((k_dots<float>), dim3(qdots, nrb, np), dim3(256), 0, s, (const float *)nullptr,
-                     (int64_t)0, 0, ca.Q, ca.ldq, ca.a, m, ca.P, ca.lp, ca.st, ca.s_q, ca.s_vec,
-                     ca.s_p);
-  // K2: e1 = a - Q c1
-  hipLaunchKernelGGL((k_rows_sub<false>), dim3(nrg, 1, np), dim3(kRowThreads), lds_t, s, ca.Q,
-                     ca.ldq, ca.a, ca.P, ca.lp, nrb, ca.e1, (double *)nullptr, m, ca.st, ca.s_q,
-                     ca.s_vec, ca.s_p, ca.s_pn);
-  // K3: c2 partials
-  hipLaunchKernelGGL((k_dots<float>), dim3(qdots, nrb, np), dim3(256), 0, s, (const float *)nullptr,
-                     (int64_t)0, 0, ca.Q, ca.ldq, ca.e1, m, ca.P, ca.lp, ca.st, ca.s_q, ca.s_vec,
-                     ca.s_p);
-  // K4: e2 = e1 - Q c2, norm partials
-  hipLaunchKernelGGL((k_rows_sub<true>), dim3(nrg, 1, np), dim3(kRowThreads), lds_t, s, ca.Q,
-                     ca.ldq, ca.e1, ca.P, ca.lp, nrb, ca.e2, ca.Pn, m, ca.st, ca.s_q, ca.s_vec,
-                     ca.s_p, ca.s_pn);
-  // K5: [B^T e2 ; V^T e2] partials (B = A: [C e2 ; V^T e2])
-  const int nfix = ca.gram ? (int)m : (int)ca.r;
-  const unsigned tdots = (unsigned)dots_col_blocks(nfix, ca.kmax);
-  if (ca.b_bf16 && !ca.gram)
-    hipLaunchKernelGGL((k_dots<uint16_t>), dim3(tdots, nrb, np), dim3(256), 0, s,
-                       (const uint16_t *)ca.B, ca.ldb, nfix, ca.V, ca.ldq, ca.e2, m, ca.P, ca.lp,
+  const dim3 gr(nrg, 1, np), br(kRowThreads);
+  const bool bf = ca.b_bf16 && !ca.gram;
+  // the slab form takes one problem with the history of omega; B = A keeps K5
+  const bool slab = ca.wh && chain_slab_fits(m, ca.gram ? 0 : ca.r, ca.kmax);
+  auto q_dots = [&](const double *x) {  // K1, K3: partials of Q^T x
+    hipLaunchKernelGGL((k_dots<float>), dim3(qdots, nrb, np), dim3(256), 0, s,
+                       (const float *)nullptr, (int64_t)0, 0, ca.Q, ca.ldq, x, m, ca.P, ca.lp,
                        ca.st, ca.s_q, ca.s_vec, ca.s_p);
-  else
-    hipLaunchKernelGGL((k_dots<float>), dim3(tdots, nrb, np), dim3(256), 0, s, (const float *)ca.B,
-                       ca.ldb, nfix, ca.V, ca.ldq, ca.e2, m, ca.P, ca.lp, ca.st, ca.s_q, ca.s_vec,
-                       ca.s_p);
+  };
+  with_row_u(ca.kmax, [&](auto uq) {
+    constexpr int UQ = decltype(uq)::value;
+    if (slab) {
+      hipLaunchKernelGGL((k_gs1<true, UQ>), gr, br, lds_t, s, *ca.A, ca.wh, ca.ldw, ca.part,
+                         ca.npart, ca.Q, ca.ldq, ca.e1, ca.P1, ca.lp1, m, ca.st);
+      if (ca.gram)
+        hipLaunchKernelGGL((k_gs2<float, true, UQ, 4>), gr, br, lds_t, s, ca.Q, ca.ldq, ca.V,
+                           (const float *)nullptr, (int64_t)0, 0, ca.e1, ca.P1, ca.lp1, ca.e2,
+                           ca.Pn, (double *)nullptr, (int64_t)0, m, ca.st);
+      else
+        with_row_u(ca.r, [&](auto ub) {
+          constexpr int UB = decltype(ub)::value;
+          if (bf)
+            hipLaunchKernelGGL((k_gs2<uint16_t, false, UQ, UB>), gr, br, lds_t, s, ca.Q, ca.ldq,
+                               ca.V, (const uint16_t *)ca.B, ca.ldb, (int)ca.r, ca.e1, ca.P1,
+                               ca.lp1, ca.e2, ca.Pn, ca.P2, ca.lp, m, ca.st);
+          else
+            hipLaunchKernelGGL((k_gs2<float, false, UQ, UB>), gr, br, lds_t, s, ca.Q, ca.ldq, ca.V,
+                               (const float *)ca.B, ca.ldb, (int)ca.r, ca.e1, ca.P1, ca.lp1, ca.e2,
+                               ca.Pn, ca.P2, ca.lp, m, ca.st);
+        });
+      return;
+    }
+    if (ca.wh) {
+      // S1 without partials: e1 = a - Q c1
+      hipLaunchKernelGGL((k_gs1<false, UQ>), gr, br, lds_t, s, *ca.A, ca.wh, ca.ldw, ca.part,
+                         ca.npart, ca.Q, ca.ldq, ca.e1, (double *)nullptr, (int64_t)0, m, ca.st);
+    } else {
+      q_dots(ca.a);  // K1: c1 partials
+      // K2: e1 = a - Q c1
+      hipLaunchKernelGGL((k_rows_sub<false, UQ>), gr, br, lds_t, s, ca.Q, ca.ldq, ca.a, ca.P, ca.lp,
+                         nrb, ca.e1, (double *)nullptr, m, ca.st, ca.s_q, ca.s_vec, ca.s_p, ca.s_pn);
+    }
+    q_dots(ca.e1);  // K3: c2 partials
+    // K4: e2 = e1 - Q c2, norm partials
+    hipLaunchKernelGGL((k_rows_sub<true, UQ>), gr, br, lds_t, s, ca.Q, ca.ldq, ca.e1, ca.P, ca.lp,
+                       nrb, ca.e2, ca.Pn, m, ca.st, ca.s_q, ca.s_vec, ca.s_p, ca.s_pn);
+  });
+  // K5: [B^T e2 ; V^T e2] partials (B = A: [C e2 ; V^T e2]); S2 formed them otherwise
+  const int nfix = ca.gram ? (int)m : (int)ca.r;
+  const bool zslab = slab && !ca.gram;
+  if (!zslab) {
+    const dim3 gd((unsigned)dots_col_blocks(nfix, ca.kmax), nrb, np);
+    if (bf)
+      hipLaunchKernelGGL((k_dots<uint16_t>), gd, dim3(256), 0, s, (const uint16_t *)ca.B, ca.ldb,
+                         nfix, ca.V, ca.ldq, ca.e2, m, ca.P, ca.lp, ca.st, ca.s_q, ca.s_vec, ca.s_p);
+    else
+      hipLaunchKernelGGL((k_dots<float>), gd, dim3(256), 0, s, (const float *)ca.B, ca.ldb, nfix,
+                         ca.V, ca.ldq, ca.e2, m, ca.P, ca.lp, ca.st, ca.s_q, ca.s_vec, ca.s_p);
+  }
   // K6
   ZArgs za{};
   za.Q = ca.Q;
   za.ldq = ca.ldq;
   za.V = ca.V;
   za.e2 = ca.e2;
-  za.P = ca.P;
+  za.P = zslab ? ca.P2 : ca.P;
   za.lp = ca.lp;
   za.nrb = nrb;
   za.Pn = ca.Pn;
@@ -713,13 +1033,24 @@ hipError_t launch_chain(const ChainArgs &ca, hipStream_t s) {
   za.s_q32 = ca.s_q32;
   za.s_io = ca.s_io;
   const size_t lds_z = (size_t)(za.r + ca.kmax + 1) * sizeof(double);
-  const dim3 gz(nrg, 1, np);
-  if (ca.gram)
-    hipLaunchKernelGGL((k_rows_z<float, true>), gz, dim3(kRowThreads), lds_z, s, za, ca.st);
-  else if (ca.b_bf16)
-    hipLaunchKernelGGL((k_rows_z<uint16_t, false>), gz, dim3(kRowThreads), lds_z, s, za, ca.st);
-  else
-    hipLaunchKernelGGL((k_rows_z<float, false>), gz, dim3(kRowThreads), lds_z, s, za, ca.st);
+  with_row_u(ca.kmax, [&](auto uq) {
+    constexpr int UQ = decltype(uq)::value;
+    if (ca.gram) {
+      hipLaunchKernelGGL((k_rows_z<float, true, false, UQ, 4>), gr, br, lds_z, s, za, ca.st);
+      return;
+    }
+    with_row_u(ca.r, [&](auto ub) {
+      constexpr int UB = decltype(ub)::value;
+      if (bf && slab)
+        hipLaunchKernelGGL((k_rows_z<uint16_t, false, true, UQ, UB>), gr, br, lds_z, s, za, ca.st);
+      else if (bf)
+        hipLaunchKernelGGL((k_rows_z<uint16_t, false, false, UQ, UB>), gr, br, lds_z, s, za, ca.st);
+      else if (slab)
+        hipLaunchKernelGGL((k_rows_z<float, false, true, UQ, UB>), gr, br, lds_z, s, za, ca.st);
+      else
+        hipLaunchKernelGGL((k_rows_z<float, false, false, UQ, UB>), gr, br, lds_z, s, za, ca.st);
+    });
+  });
   return hipGetLastError();
 }
 

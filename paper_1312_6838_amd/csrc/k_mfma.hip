@@ -1936,15 +1936,46 @@ __global__ void k_qta_reduce(const double *__restrict__ part, int nwg, int kpad,
   quad[s] = acc;
 }
 
-// obj[s+1] = F0 - sum_{x<=s} quad[x] for s < t (the objective from exact decrements)
-__global__ void k_obj_from_quad(const double *F0, const double *quad, const DevState *st,
-                                double *obj) {
-  if (threadIdx.x != 0) return;
+// obj[s+1] = F0 - sum_{x<=s} quad[x] for s < t (the objective from exact
+// decrements).  qpart: quad[s] is first formed as the sum of row s of qpart
+// (nq per-workgroup sums), one wave per row.  The running difference is
+// serial, over values held in LDS (from memory, 200 steps took 27 us).
+constexpr int kObjChunk = 1024;
+__global__ __launch_bounds__(kObjChunk) void k_obj_from_quad(const double *F0, const double *qpart,
+                                                             int nq, double *quad,
+                                                             const DevState *st, double *obj) {
+  __shared__ double q[kObjChunk];
+  __shared__ double Fs;
   const int t = st->t;
-  double F = *F0;
-  for (int s = 0; s < t; ++s) {
-    F -= quad[s];
-    obj[s + 1] = F;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (threadIdx.x == 0) Fs = *F0;
+  for (int s0 = 0; s0 < t; s0 += kObjChunk) {
+    const int ns = t - s0 < kObjChunk ? t - s0 : kObjChunk;
+    if (qpart) {
+      for (int s = wave; s < ns; s += kObjChunk / 64) {
+        double a = 0.0;
+        for (int x = lane; x < nq; x += 64) a += qpart[(int64_t)(s0 + s) * nq + x];
+        a = wave_sum(a);
+        if (lane == 0) {
+          q[s] = a;
+          quad[s0 + s] = a;
+        }
+      }
+    } else if ((int)threadIdx.x < ns) {
+      q[threadIdx.x] = quad[s0 + threadIdx.x];
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      double F = Fs;
+      for (int s = 0; s < ns; ++s) {
+        F -= q[s];
+        q[s] = F;
+      }
+      Fs = F;
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < ns) obj[s0 + threadIdx.x + 1] = q[threadIdx.x];
+    __syncthreads();
   }
 }
 
@@ -1976,9 +2007,9 @@ hipError_t launch_qta(const double *Q, int64_t ldq, int kmax, const DevState *st
   return hipGetLastError();
 }
 
-hipError_t launch_obj_from_quad(const double *F0, const double *quad, const DevState *st,
-                                double *obj, hipStream_t s) {
-  hipLaunchKernelGGL(k_obj_from_quad, dim3(1), dim3(64), 0, s, F0, quad, st, obj);
+hipError_t launch_obj_from_quad(const double *F0, const double *qpart, int nq, double *quad,
+                                const DevState *st, double *obj, hipStream_t s) {
+  hipLaunchKernelGGL(k_obj_from_quad, dim3(1), dim3(kObjChunk), 0, s, F0, qpart, nq, quad, st, obj);
   return hipGetLastError();
 }
 

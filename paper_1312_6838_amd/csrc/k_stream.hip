@@ -6,8 +6,9 @@
 //     f_i <- f_i - 2 omega_i gamma_i + ||upsilon||^2 omega_i^2
 //     g_i <- g_i - omega_i^2
 // and the column's score f_i / g_i enters the argmax of the next pick.
-// The last workgroup to finish reduces the per-workgroup winners and writes
-// the next pick into the device state.
+// The per-workgroup winners are reduced by the chain that follows (its first
+// kernel), or, without one that does, by the last workgroup to finish, which
+// writes the next pick into the device state.
 //
 // Work mapping (CDNA4, 64-lane wavefronts, 512-thread workgroups, one per CU):
 //   * a "team" of W wavefronts streams a sequence of work units of ucol
@@ -65,7 +66,8 @@ __global__ __launch_bounds__(512) void k_stream(AView A, int ucol, const float *
                                                 double *__restrict__ ap64, int score_only,
                                                 double *__restrict__ qpart,
                                                 double *__restrict__ quad,
-                                                float *__restrict__ emb, int64_t ldw) {
+                                                float *__restrict__ emb, int64_t ldw,
+                                                float *__restrict__ wh, int defer) {
   constexpr int EPC = Elem<DT>::epc;
   constexpr int TEAMS = kStreamWaves / W;
   constexpr int U = (8 / NJ) > 0 ? (8 / NJ) : 1;  // columns per load group
@@ -83,6 +85,8 @@ __global__ __launch_bounds__(512) void k_stream(AView A, int ucol, const float *
   const bool rescore = score_only || st->skip;
   // embedding: row t - 1 of W = Q^T A receives omega = A^T q_t
   float *const wrow = (emb != nullptr && !rescore) ? emb + (int64_t)(st->t - 1) * ldw : nullptr;
+  // the chain's history of omega: the same, row t - 1 of (kmax, n)
+  float *const hrow = (wh != nullptr && !rescore) ? wh + (int64_t)(st->t - 1) * A.n : nullptr;
   const double u2 = st->u2;
   const double tau = st->tau;
 
@@ -276,6 +280,7 @@ __global__ __launch_bounds__(512) void k_stream(AView A, int ucol, const float *
       gv = gv - ww * ww;
       if constexpr (EX) qacc += mine ? ww * ww : 0.0;
       if (wrow != nullptr && mine) wrow[col] = (float)ww;
+      if (hrow != nullptr && mine) hrow[col] = (float)ww;
     }
     const bool elig = mine && mk == 0 && gv > tau * g0v && isfinite(fv) && isfinite(gv);
     const double scv = fv / gv;
@@ -317,8 +322,13 @@ __global__ __launch_bounds__(512) void k_stream(AView A, int ucol, const float *
       }
     part[blockIdx.x].score = b;
     part[blockIdx.x].idx = bi;
-    if constexpr (EX) qpart[blockIdx.x] = sum_waves(qs);
+    if constexpr (EX)
+      if (!rescore) qpart[defer ? (int64_t)(st->t - 1) * gridDim.x + blockIdx.x : blockIdx.x] = sum_waves(qs);
   }
+  // the chain takes the next pick from the winners, and the final objective
+  // sums the decreases: the arrival of all workgroups and the last one's
+  // reductions behind it cost about 5 us a pass
+  if (defer) return;
   if (!last_block_arrive(&st->cnt[0])) return;
 
   // last workgroup: the exact decrease of this step (EX) ...
@@ -422,7 +432,7 @@ static int pow2_at_least(int64_t x) {
 
 typedef void (*StreamFn)(AView, int, const float *, const double *, const float *, double *,
                          double *, const double *, const uint8_t *, ArgPart *, DevState *, double *,
-                         int, double *, double *, float *, int64_t);
+                         int, double *, double *, float *, int64_t, float *, int);
 
 template <int DT, int NJ, int W, bool EX>
 static StreamFn pick_pd(int pd) {
@@ -537,13 +547,13 @@ hipError_t launch_stream(const StreamGeo &geo, const AView &A, const float *q32,
                          const double *q64, const float *z32, double *f, double *g,
                          const double *g0, uint8_t *mask, ArgPart *part, DevState *st,
                          double *ap64, int score_only, double *qpart, double *quad,
-                         float *emb, int64_t ldw, hipStream_t s) {
+                         float *emb, int64_t ldw, float *wh, bool defer, hipStream_t s) {
   const bool ex = qpart != nullptr;
   StreamFn fn = pick_kernel(A.dtype, geo.nj, geo.w, geo.pd, ex);
   if (!fn) return hipErrorInvalidValue;
   hipLaunchKernelGGL(fn, dim3(ex ? geo.grid_ex : geo.grid), dim3(kStreamThreads), 0, s, A,
                      ex ? geo.ucol_ex : geo.ucol, q32, q64, z32, f, g, g0, mask, part, st, ap64,
-                     score_only, qpart, quad, emb, ldw);
+                     score_only, qpart, quad, emb, ldw, wh, (int)defer);
   return hipGetLastError();
 }
 
