@@ -93,7 +93,7 @@ EigLayout eig_layout(int64_t m, int64_t ldq, int s, int num_cu) {
   return E;
 }
 
-bool make_layout_with(const gcss_desc *d, int num_cu, bool hist, Layout *L) {
+bool make_layout_with(const gcss_desc *d, int num_cu, bool hist, bool basis, Layout *L) {
   const int64_t m = d->m, n = d->n, k = d->k_max, r = d->r_max;
   L->ldq = ld_for(m);
   L->geo = stream_geometry(m, n, d->a_dtype, num_cu);
@@ -164,24 +164,26 @@ bool make_layout_with(const gcss_desc *d, int num_cu, bool hist, Layout *L) {
     const int64_t smax = std::min<int64_t>(std::min<int64_t>(k, m), kRankMaxL);
     s = std::max(s, eig_layout(m, L->ldq, (int)smax, num_cu).bytes);
   }
+  if (basis) s = std::max(s, basis_plan(m, L->ldq, (int)k).bytes);
   L->scratch_bytes = s;
   L->scratch = c.take<uint8_t>(s);
   L->total = up(c.off, 256);
   return true;
 }
 
-// The chain's history of omega costs 4 k_max n bytes; it is kept while that is
-// at most a quarter of A's own (k_max <= lda * element size / 16) or 16 MiB,
-// so it never dominates what a context needs, and where it does not push a
-// problem out of the static workspace (which takes the same layout as a
-// context, so that both run the same kernels).
+// Two parts of the workspace only make calls faster: the chain's history of
+// omega (4 k_max n bytes; kept while that is at most a quarter of A's own,
+// k_max <= lda * element size / 16, or 16 MiB, so it never dominates what a
+// context needs) and the scratch of a subset's basis.  Neither may push a
+// problem out of the static workspace, which takes the same layout as a
+// context so that both run the same kernels.
 bool make_layout(const gcss_desc *d, int num_cu, Layout *L) {
   const int64_t hb = 4 * (int64_t)d->k_max * d->n;
-  const bool want = hb <= std::max<int64_t>(d->n * d->lda * dtype_bytes(d->a_dtype) / 4, 16 << 20);
-  if (!make_layout_with(d, num_cu, want, L)) return false;
-  if (L->hist && L->total > (size_t)GCSS_STATIC_SCRATCH_BYTES) {
+  const bool hist = hb <= std::max<int64_t>(d->n * d->lda * dtype_bytes(d->a_dtype) / 4, 16 << 20);
+  if (!make_layout_with(d, num_cu, hist, true, L)) return false;
+  if (L->total > (size_t)GCSS_STATIC_SCRATCH_BYTES) {
     Layout S;
-    if (make_layout_with(d, num_cu, false, &S) && S.total <= (size_t)GCSS_STATIC_SCRATCH_BYTES) *L = S;
+    if (make_layout_with(d, num_cu, false, false, &S) && S.total <= (size_t)GCSS_STATIC_SCRATCH_BYTES) *L = S;
   }
   return true;
 }
@@ -891,21 +893,44 @@ gcss_status gcss_reconstruction_error(gcss_ctx *h, const int64_t *idx, int32_t k
   int kb = k;  // basis size
   const bool reuse = h->basis_valid && k <= (int)h->last_idx.size() &&
                      std::equal(v.begin(), v.end(), h->last_idx.begin());
+  // A basis the last selection did not build: all columns at once where that
+  // fits the scratch and is certified (from kBasisBlock columns on: its dozen
+  // launches cost what Gram-Schmidt takes for about that many), else
+  // Gram-Schmidt column by column, which drops dependent columns.
+  constexpr int kBasisBlock = 8;
+  const BasisPlan bp = basis_plan(m, ldq, k);
+  bool block = !reuse && k >= kBasisBlock && k <= m && bp.bytes <= h->L.scratch_bytes;
   if (!reuse && k > 0) {
-    int64_t *pick = h->at<int64_t>(h->L.pick);
-    HIPCHK(hipMemcpyAsync(pick, v.data(), sizeof(int64_t) * k, hipMemcpyHostToDevice, s));
-    const StepBufs sb = h->bufs(pick, 1);
-    // fresh state in basis-only mode
-    HIPCHK(launch_select_begin(h->at<double>(h->L.f0), h->at<double>(h->L.g0), h->at<uint8_t>(h->L.mask0),
-                               h->at<double>(h->L.f), h->at<double>(h->L.g), h->at<uint8_t>(h->L.mask),
-                               h->d.n, sb, k, h->d.k_max, h->F0(), kBasisTau, s));
-    for (int i = 0; i < k; ++i) HIPCHK(enqueue_basis_step(h, sb));
-    DevState hs;
-    HIPCHK(hipMemcpyAsync(&hs, sb.st, sizeof hs, hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
-    kb = hs.t;
+    HIPCHK(hipMemcpyAsync(h->at<int64_t>(h->L.pick), v.data(), sizeof(int64_t) * k, hipMemcpyHostToDevice, s));
     h->basis_valid = false;
     h->q_from_select = false;
+  }
+  for (;;) {
+    if (!reuse && k > 0) {
+      int64_t *pick = h->at<int64_t>(h->L.pick);
+      const StepBufs sb = h->bufs(pick, 1);
+      // fresh state in basis-only mode
+      HIPCHK(launch_select_begin(h->at<double>(h->L.f0), h->at<double>(h->L.g0), h->at<uint8_t>(h->L.mask0),
+                                 h->at<double>(h->L.f), h->at<double>(h->L.g), h->at<uint8_t>(h->L.mask),
+                                 h->d.n, sb, k, h->d.k_max, h->F0(), kBasisTau, s));
+      if (block) {
+        HIPCHK(launch_basis(bp, h->at<char>(h->L.scratch), h->A, pick, k, h->at<double>(h->L.Q), ldq, sb.st, s));
+        int bad = 0;
+        HIPCHK(hipMemcpyAsync(&bad, h->at<char>(h->L.scratch) + bp.flag, sizeof bad, hipMemcpyDeviceToHost, s));
+        HIPCHK(hipStreamSynchronize(s));
+        if (bad) {
+          block = false;
+          continue;
+        }
+      } else {
+        for (int i = 0; i < k; ++i) HIPCHK(enqueue_basis_step(h, sb));
+        DevState hs;
+        HIPCHK(hipMemcpyAsync(&hs, sb.st, sizeof hs, hipMemcpyDeviceToHost, s));
+        HIPCHK(hipStreamSynchronize(s));
+        kb = hs.t;
+      }
+    }
+    break;
   }
   const double *Q = h->at<double>(h->L.Q);
   char *scr = h->at<char>(h->L.scratch);

@@ -244,6 +244,19 @@ size_t chain_block_lds_bytes(int64_t m, int64_t r, int kmax);
 bool chain_block_fits(int64_t m, int64_t r, int kmax, size_t lds_max);
 hipError_t launch_chain_block(const ChainArgs &ca, hipStream_t s);
 
+// ---- basis of a caller's columns (k_basis.hip) ----
+struct BasisPlan {
+  int nsplit;
+  int64_t rows;  // per split
+  size_t S, Y, part, W, flag, bytes;
+};
+BasisPlan basis_plan(int64_t m, int64_t ldq, int kmax);
+// Q[:, 0..k) = an orthonormal basis of the columns pick[0..k) of A, in their
+// order, state t = k; the int at scr + P.flag is 1 where it is not certified
+// (the caller then runs Gram-Schmidt), else 0
+hipError_t launch_basis(const BasisPlan &P, char *scr, const AView &A, const int64_t *pick, int k,
+                        double *Q, int64_t ldq, DevState *st, hipStream_t s);
+
 // ---- launchers (k_mfma.hip) ----
 // f0_i = scale_i^2 * || X^T A_i ||^2 (X: m x R, K-contiguous, ldx), g0_i, mask0_i
 hipError_t launch_init_factor(const float *X, int64_t ldx, int64_t R, const AView &A,
