@@ -68,6 +68,7 @@ struct StreamGeo {
   int ucol;      // columns per team in one work unit of the queue
   int upw;       // work units per workgroup the unit size aims at
   int occ;       // resident workgroups per CU of the chosen kernel
+  bool big;      // A is larger than the last-level cache
 };
 
 // ---- launchers (k_stream.hip) ----

@@ -131,9 +131,9 @@ __global__ __launch_bounds__(256) void k_stream_b(AView A, const GroupEnt *__res
       tau = st->tau;
       if (ws == 0) {
         const int64_t colc = col0 + (lane < ncol ? lane : 0);
-        fv = f[colc];
-        gv = g[colc];
-        g0v = g0[colc];
+        fv = __builtin_nontemporal_load(f + colc);
+        gv = __builtin_nontemporal_load(g + colc);
+        g0v = __builtin_nontemporal_load(g0 + colc);
         mk = mask[colc];
         if constexpr (DT == DT_FP8) scv = A.scale[colc];
       }
@@ -246,8 +246,8 @@ __global__ __launch_bounds__(256) void k_stream_b(AView A, const GroupEnt *__res
           const double w = s * (double)mw, y = s * (double)mz;
           fv = fv - 2.0 * w * y + u2 * w * w;
           gv = gv - w * w;
-          f[col] = fv;
-          g[col] = gv;
+          __builtin_nontemporal_store(fv, f + col);
+          __builtin_nontemporal_store(gv, g + col);
         }
         if (mk == 0 && gv > tau * g0v && isfinite(fv) && isfinite(gv)) {
           best = fv / gv;
@@ -263,8 +263,10 @@ __global__ __launch_bounds__(256) void k_stream_b(AView A, const GroupEnt *__res
     __syncthreads();
     sg = sg_s;
   }
-  if (!last_block_arrive(&bcnt[0])) return;
-  if (threadIdx.x == 0) {
+  // the last workgroup re-arms the claims; nothing it reads was written by the
+  // others, so the arrival needs no fence
+  if (threadIdx.x == 0 && __hip_atomic_fetch_add(&bcnt[0], 1u, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1) {
     bcnt[0] = 0;
     bcnt[1] = 0;
   }

@@ -34,6 +34,18 @@ __device__ __forceinline__ uint4 load_chunk(const char *p) {
   return make_uint4(v[0], v[1], v[2], v[3]);
 }
 
+// Loads and stores that bypass the caches (NT) or not.
+template <bool NT, typename T>
+__device__ __forceinline__ T load_once(const T *p) {
+  if constexpr (NT) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+template <bool NT, typename T>
+__device__ __forceinline__ void store_once(T v, T *p) {
+  if constexpr (NT) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
+
 // One workgroup of 8 waves per CU (at the kernel's occupancy of two waves per
 // SIMD): two 4-wave workgroups on one CU split its bandwidth unevenly (the
 // older one's loads win), which left the younger finishing alone.
@@ -47,6 +59,14 @@ __device__ __forceinline__ double sum_waves(const double (&v)[kStreamWaves]) {
   return s;
 }
 
+// Units whose results a workgroup holds in LDS (1536 bytes each): 144 KB where
+// the registers leave room for one workgroup per CU anyway (from 16 elements
+// of q and z per lane on), else half of that, so that two still fit.
+constexpr int stream_hold(int elems) { return elems >= 16 ? 96 : 48; }
+// Waves per SIMD the registers are limited for: two workgroups per CU for the
+// smallest column parts of the FP32-dot pass, else one.
+constexpr int stream_waves(int elems, int epc, bool ex) { return elems <= 8 && epc == 4 && !ex ? 4 : 2; }
+
 // (FP64 sums, EX only, keep the shuffle butterfly: DPP on both halves of each
 // double measured no faster)
 __device__ __forceinline__ double wave_total(double v) { return wave_sum(v); }
@@ -55,8 +75,12 @@ __device__ __forceinline__ double wave_total(double v) { return wave_sum(v); }
 // basis vector (every product of a decoded element and q is exact before the
 // FP64 accumulation), and the pass also returns sum_i omega_i^2 = ||A^T q||^2,
 // the exact decrease of the objective, in quad[t - 1].
-template <int DT, int NJ, int W, int PD, bool EX>
-__global__ __launch_bounds__(512) void k_stream(AView A, int ucol, const float *__restrict__ q32,
+// BIG (A larger than the last-level cache): the results are held in LDS and
+// written in a burst, past the caches like the scores' loads; a smaller matrix
+// keeps its scores in the caches, and stores each unit's as it goes.
+template <int DT, int NJ, int W, int PD, bool EX, bool BIG>
+__global__ __launch_bounds__(512, BIG ? stream_waves(NJ *Elem<DT>::epc, Elem<DT>::epc, EX) : 0) void k_stream(
+                                                AView A, int ucol, const float *__restrict__ q32,
                                                 const double *__restrict__ q64,
                                                 const float *__restrict__ z32,
                                                 double *__restrict__ f, double *__restrict__ g,
@@ -77,6 +101,15 @@ __global__ __launch_bounds__(512) void k_stream(AView A, int ucol, const float *
   __shared__ double bs[kStreamWaves];
   __shared__ int64_t bi_s[kStreamWaves];
   __shared__ double qs[kStreamWaves];
+  // results of a team's units, held until the end of its range (or until the
+  // buffer is full): writes of f and g among the reads of A cost far more than
+  // their bytes (2048 x 2^20 FP32: 20 MB of 8.6 GB took 7% of the pass, as
+  // measured without them), a burst of writes at the end hardly anything.
+  // (not where the registers are full: the FP64-dot pass with 32 elements of a
+  // 16- or 8-bit type per lane would spill)
+  constexpr bool HOLD = BIG && !(EX && EPC > 4 && NJ * EPC == 32);
+  constexpr int CAP = HOLD ? stream_hold(NJ * EPC) / TEAMS : 1;  // units per team
+  __shared__ double held_s[HOLD ? TEAMS * CAP : 1][3][64];  // f, g, omega (binary32) of a unit's columns
 
   // after the last pick (done) one more pass runs for that pick's exact
   // decrease (EX) or its row of the embedding, without scores or a next pick
@@ -215,6 +248,7 @@ __global__ __launch_bounds__(512) void k_stream(AView A, int ucol, const float *
       mz = me ? dz : mz;
     }
   };
+  int held = 0;
   // one instance of the unit loop for full-height chunks, one for a ragged m
   auto run = [&](auto full_c) {
   if (!rescore) {
@@ -232,8 +266,8 @@ __global__ __launch_bounds__(512) void k_stream(AView A, int ucol, const float *
     const bool mine = ws == 0 && lane < ncol;
     const int64_t col = c0 + (lane < ncol ? lane : 0);
     const int64_t colc = col < n ? col : n - 1;
-    double fv = f[colc], gv = g[colc];
-    const double g0v = g0[colc];
+    double fv = load_once<BIG>(f + colc), gv = load_once<BIG>(g + colc);
+    const double g0v = load_once<BIG>(g0 + colc);
     const int mk = mask[colc];
     float sc = 1.f;
     if constexpr (DT == DT_FP8) sc = A.scale[colc];
@@ -279,18 +313,45 @@ __global__ __launch_bounds__(512) void k_stream(AView A, int ucol, const float *
       fv = fv - 2.0 * ww * y + u2 * ww * ww;
       gv = gv - ww * ww;
       if constexpr (EX) qacc += mine ? ww * ww : 0.0;
-      if (wrow != nullptr && mine) wrow[col] = (float)ww;
-      if (hrow != nullptr && mine) hrow[col] = (float)ww;
+      if constexpr (HOLD) {
+        if (ws == 0) {
+          double *const h = &held_s[team * CAP + held][0][lane];
+          h[0] = fv;
+          h[64] = gv;
+          *(float *)(h + 128) = (float)ww;
+        }
+      } else {
+        if (wrow != nullptr && mine) store_once<BIG>((float)ww, wrow + col);
+        if (hrow != nullptr && mine) store_once<BIG>((float)ww, hrow + col);
+      }
     }
     const bool elig = mine && mk == 0 && gv > tau * g0v && isfinite(fv) && isfinite(gv);
     const double scv = fv / gv;
-    if (mine && !rescore && !qonly) {
-      f[col] = fv;
-      g[col] = gv;
+    if (!HOLD && mine && !rescore && !qonly) {
+      store_once<BIG>(fv, f + col);
+      store_once<BIG>(gv, g + col);
     }
     if (elig && better(scv, col, best, besti)) {
       best = scv;
       besti = col;
+    }
+    if (HOLD) ++held;
+    if (HOLD && ws == 0 && !rescore && (held == CAP || su_nxt >= nsu)) {
+      // units kth - held + 1 .. kth
+      int64_t c = (((int64_t)blockIdx.x * per + kth + 1 - held) * TEAMS + team) * ucol + lane;
+      for (int u = 0; u < held; ++u, c += (int64_t)TEAMS * ucol) {
+        if (lane < ucol && c < n) {
+          const double *const h = &held_s[team * CAP + u][0][lane];
+          if (!qonly) {
+            __builtin_nontemporal_store(h[0], f + c);
+            __builtin_nontemporal_store(h[64], g + c);
+          }
+          const float w = *(const float *)(h + 128);
+          if (wrow != nullptr) __builtin_nontemporal_store(w, wrow + c);
+          if (hrow != nullptr) __builtin_nontemporal_store(w, hrow + c);
+        }
+      }
+      held = 0;
     }
     ++kth;
     su_cur = su_nxt;
@@ -435,44 +496,45 @@ typedef void (*StreamFn)(AView, int, const float *, const double *, const float 
                          int, double *, double *, float *, int64_t, float *, int);
 
 template <int DT, int NJ, int W, bool EX>
-static StreamFn pick_pd(int pd) {
-  return pd >= 2 ? (StreamFn)k_stream<DT, NJ, W, 2, EX> : (StreamFn)k_stream<DT, NJ, W, 1, EX>;
+static StreamFn pick_pd(int pd, bool big) {
+  if (big) return pd >= 2 ? (StreamFn)k_stream<DT, NJ, W, 2, EX, true> : (StreamFn)k_stream<DT, NJ, W, 1, EX, true>;
+  return pd >= 2 ? (StreamFn)k_stream<DT, NJ, W, 2, EX, false> : (StreamFn)k_stream<DT, NJ, W, 1, EX, false>;
 }
 
 template <int DT, int NJ, bool EX>
-static StreamFn pick_w(int w, int pd) {
+static StreamFn pick_w(int w, int pd, bool big) {
   switch (w) {
-    case 1: return pick_pd<DT, NJ, 1, EX>(pd);
-    case 2: return pick_pd<DT, NJ, 2, EX>(pd);
-    case 4: return pick_pd<DT, NJ, 4, EX>(pd);
+    case 1: return pick_pd<DT, NJ, 1, EX>(pd, big);
+    case 2: return pick_pd<DT, NJ, 2, EX>(pd, big);
+    case 4: return pick_pd<DT, NJ, 4, EX>(pd, big);
   }
   return nullptr;
 }
 
 // q and z live in registers: at most 32 elements each per lane.
 template <int DT, bool EX>
-static StreamFn pick_nj(int nj, int w, int pd) {
+static StreamFn pick_nj(int nj, int w, int pd, bool big) {
   constexpr int NJMAX = 32 / Elem<DT>::epc;
   switch (nj) {
-    case 1: return pick_w<DT, 1, EX>(w, pd);
+    case 1: return pick_w<DT, 1, EX>(w, pd, big);
     case 2:
-      if constexpr (NJMAX >= 2) return pick_w<DT, 2, EX>(w, pd);
+      if constexpr (NJMAX >= 2) return pick_w<DT, 2, EX>(w, pd, big);
       break;
     case 4:
-      if constexpr (NJMAX >= 4) return pick_w<DT, 4, EX>(w, pd);
+      if constexpr (NJMAX >= 4) return pick_w<DT, 4, EX>(w, pd, big);
       break;
     case 8:
-      if constexpr (NJMAX >= 8) return pick_w<DT, 8, EX>(w, pd);
+      if constexpr (NJMAX >= 8) return pick_w<DT, 8, EX>(w, pd, big);
       break;
   }
   return nullptr;
 }
 
-static StreamFn pick_kernel(int dtype, int nj, int w, int pd, bool ex) {
+static StreamFn pick_kernel(int dtype, int nj, int w, int pd, bool ex, bool big) {
   switch (dtype) {
-    case DT_F32: return ex ? pick_nj<DT_F32, true>(nj, w, pd) : pick_nj<DT_F32, false>(nj, w, pd);
-    case DT_BF16: return ex ? pick_nj<DT_BF16, true>(nj, w, pd) : pick_nj<DT_BF16, false>(nj, w, pd);
-    case DT_FP8: return ex ? pick_nj<DT_FP8, true>(nj, w, pd) : pick_nj<DT_FP8, false>(nj, w, pd);
+    case DT_F32: return ex ? pick_nj<DT_F32, true>(nj, w, pd, big) : pick_nj<DT_F32, false>(nj, w, pd, big);
+    case DT_BF16: return ex ? pick_nj<DT_BF16, true>(nj, w, pd, big) : pick_nj<DT_BF16, false>(nj, w, pd, big);
+    case DT_FP8: return ex ? pick_nj<DT_FP8, true>(nj, w, pd, big) : pick_nj<DT_FP8, false>(nj, w, pd, big);
   }
   return nullptr;
 }
@@ -500,6 +562,11 @@ StreamGeo stream_geometry(int64_t m, int64_t n, int dtype, int num_cu) {
   geo.g = 64;  // column groups of the batched pass
   geo.pd = 1;
   geo.upw = 4;
+  // MI355X's last-level cache.  Held and written past the caches against
+  // stored as it goes: 8.6 GB 127.4 against 133.0 ms (100 passes), 2.1 GB 179.4
+  // against 184.1 ms (500), 1.07 GB 53.0 against 53.2 ms; 240 MB 4.34 against
+  // 4.29 ms (64), 123 MB 2.33 against 2.30 ms (50).
+  geo.big = m * n * dtype_bytes(dtype) > (int64_t)256 << 20;
   const int teams = 4 / w;
   const int64_t need = (n + teams - 1) / teams;
   const int64_t cap = 8LL * num_cu;  // upper bound: 8 workgroups (32 waves) per CU
@@ -513,7 +580,7 @@ StreamGeo stream_geometry(int64_t m, int64_t n, int dtype, int num_cu) {
 // the unit size for about upw units per workgroup, a multiple of the ring
 static hipError_t finalize_one(const StreamGeo &geo, int64_t n, int dtype, int num_cu, bool ex,
                                int *grid, int *ucol) {
-  StreamFn fn = pick_kernel(dtype, geo.nj, geo.w, geo.pd, ex);
+  StreamFn fn = pick_kernel(dtype, geo.nj, geo.w, geo.pd, ex, geo.big);
   if (!fn) return hipErrorInvalidValue;
   int per_cu = 0;
   hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)fn, kStreamThreads, 0);
@@ -549,7 +616,7 @@ hipError_t launch_stream(const StreamGeo &geo, const AView &A, const float *q32,
                          double *ap64, int score_only, double *qpart, double *quad,
                          float *emb, int64_t ldw, float *wh, bool defer, hipStream_t s) {
   const bool ex = qpart != nullptr;
-  StreamFn fn = pick_kernel(A.dtype, geo.nj, geo.w, geo.pd, ex);
+  StreamFn fn = pick_kernel(A.dtype, geo.nj, geo.w, geo.pd, ex, geo.big);
   if (!fn) return hipErrorInvalidValue;
   hipLaunchKernelGGL(fn, dim3(ex ? geo.grid_ex : geo.grid), dim3(kStreamThreads), 0, s, A,
                      ex ? geo.ucol_ex : geo.ucol, q32, q64, z32, f, g, g0, mask, part, st, ap64,
