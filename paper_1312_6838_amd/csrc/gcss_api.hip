@@ -1224,7 +1224,7 @@ bool make_blayout(const gcss_desc *d, const Layout &L, int nblocks, int kb, int 
     B->mex = c.take<uint8_t>(P);
     B->mW = c.take<double>((size_t)(km + 1) * P);
     B->mU = c.take<double>((size_t)(km + 1) * r);
-    B->mpart = c.take<ArgPart>(merge_step_groups(P));
+    B->mpart = c.take<ArgPart>(2 * (size_t)merge_step_groups(P));
   }
   if (km > P) return false;
   gcss_desc sd = sub_desc(d, P, km);

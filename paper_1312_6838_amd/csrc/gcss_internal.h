@@ -402,7 +402,7 @@ struct MergeArgs {
   uint8_t *excl;       // P: 1 picked, 2 dropped by the basis check
   double *W;           // k x P, row s = omega^(s)
   double *U;           // k x r, row s = upsilon^(s)
-  ArgPart *part;       // one per step workgroup
+  ArgPart *part;       // two per step workgroup
   DevState *st;
   int64_t *loc;        // k picks (pool positions), -1 past the last
   double *obj;         // k + 1
