@@ -694,7 +694,7 @@ gcss_status gcss_set_target(gcss_ctx *h, const void *b, int32_t b_dtype, int64_t
     float *C = h->at<float>(h->L.gram);
     HIPCHK(launch_gram(h->A, C, h->L.ldq, h->at<void>(h->L.scratch), h->num_cu, h->stream));
     HIPCHK(launch_init_gram(C, h->L.ldq, h->A, h->at<double>(h->L.f0), h->at<double>(h->L.g0),
-                            h->at<uint8_t>(h->L.mask0), h->stream));
+                            h->at<uint8_t>(h->L.mask0), h->at<void>(h->L.scratch), h->L.scratch_bytes, h->stream));
     HIPCHK(launch_sum_f64(h->at<double>(h->L.g0), h->d.n, h->F0(), h->at<double>(h->L.npart), 1024, h->stream));
     h->target = 2;
     h->B = nullptr;
@@ -722,7 +722,7 @@ gcss_status gcss_set_target(gcss_ctx *h, const void *b, int32_t b_dtype, int64_t
       ldbf = h->L.ldq;
     }
     HIPCHK(launch_init_factor(bf, ldbf, r, h->A, h->at<double>(h->L.f0), h->at<double>(h->L.g0),
-                              h->at<uint8_t>(h->L.mask0), h->stream));
+                              h->at<uint8_t>(h->L.mask0), h->at<void>(h->L.scratch), h->L.scratch_bytes, h->stream));
     // (the step buffer for upsilon, r_max + 8 doubles, is free here)
     HIPCHK(launch_sumsq_f32(bf, m, r, ldbf, h->F0(), h->at<double>(h->L.ups), h->stream));
     h->target = 1;

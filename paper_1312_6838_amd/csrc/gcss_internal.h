@@ -259,12 +259,15 @@ hipError_t launch_basis(const BasisPlan &P, char *scr, const AView &A, const int
                         double *Q, int64_t ldq, DevState *st, hipStream_t s);
 
 // ---- launchers (k_mfma.hip) ----
+// (scratch: parts of f where few columns share their rows' chunks)
 // f0_i = scale_i^2 * || X^T A_i ||^2 (X: m x R, K-contiguous, ldx), g0_i, mask0_i
 hipError_t launch_init_factor(const float *X, int64_t ldx, int64_t R, const AView &A,
-                              double *f0, double *g0, uint8_t *mask0, hipStream_t s);
+                              double *f0, double *g0, uint8_t *mask0, void *scratch,
+                              size_t scratch_bytes, hipStream_t s);
 // f0_i = scale_i^2 * A_i^T C A_i (C: m x m symmetric, ldc), g0_i, mask0_i
 hipError_t launch_init_gram(const float *C, int64_t ldc, const AView &A, double *f0,
-                            double *g0, uint8_t *mask0, hipStream_t s);
+                            double *g0, uint8_t *mask0, void *scratch, size_t scratch_bytes,
+                            hipStream_t s);
 // C = A A^T (m x m, ldc) using split-K partials in scratch (bytes >= gram_scratch_bytes)
 size_t gram_scratch_bytes(int64_t m, int64_t n, int64_t ldc, int num_cu);
 hipError_t launch_gram(const AView &A, float *C, int64_t ldc, void *scratch, int num_cu,

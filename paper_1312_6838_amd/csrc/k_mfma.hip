@@ -195,11 +195,17 @@ __device__ __forceinline__ float4 load4(const void *base, int64_t off) {
 // RT = 64*RB; the column results are accumulated across chunks.  With TRI,
 // X = C is weighted as T/2 (zero left of the diagonal, so the k loop starts
 // at r0; one half on it) and the sum is doubled.
+//
+// Few columns leave most of the chip idle (one workgroup per NT of them), so
+// then the row chunks are shared by gridDim.y workgroups: y takes the chunks
+// y, y + gridDim.y, ... and writes its part of f to fp[y * n + j] (y = 0 also
+// g), which k_init_finish adds in order.
 template <int DT, int RB, int NB, int BKT, bool TRI, bool DB>
 __global__ __launch_bounds__(256) void k_init(const float *__restrict__ X, int64_t ldx,
                                               int64_t R, AView A, double *__restrict__ f0,
                                               double *__restrict__ g0,
-                                              uint8_t *__restrict__ mask0) {
+                                              uint8_t *__restrict__ mask0,
+                                              double *__restrict__ fp) {
   constexpr int RT = 64 * RB, NT = 16 * NB, KP = BKT + 4;
   constexpr int ES = EInfo<DT>::esize, EPC = EInfo<DT>::epc;
   constexpr int XQ = BKT / 4;              // float4 per X row per stage
@@ -229,7 +235,7 @@ __global__ __launch_bounds__(256) void k_init(const float *__restrict__ X, int64
 
   const int64_t nchunks = (R + RT - 1) / RT;
   const int64_t ksteps = (m + BKT - 1) / BKT;
-  for (int64_t rc = 0; rc < nchunks; ++rc) {
+  for (int64_t rc = blockIdx.y; rc < nchunks; rc += gridDim.y) {
     const int64_t r0 = rc * RT;
     f32x4 acc[RB][NB];
 #pragma unroll
@@ -391,6 +397,11 @@ __global__ __launch_bounds__(256) void k_init(const float *__restrict__ X, int64
     if (j < n) {
       const double fv = ((red[0][tid] + red[1][tid]) + red[2][tid]) + red[3][tid];
       const double sc = col_scale(A, j);
+      if (gridDim.y > 1) {
+        fp[(int64_t)blockIdx.y * n + j] = fv;
+        if (blockIdx.y == 0) g0[j] = sc * sc * gs[tid];
+        return;
+      }
       const double f = (TRI ? 2.0 : 1.0) * sc * sc * fv, g = sc * sc * gs[tid];
       f0[j] = f;
       g0[j] = g;
@@ -635,12 +646,16 @@ __global__ __launch_bounds__(kI2Threads, 1) void k_init256(const float *__restri
 // LDS store.  One workgroup per 256 columns of A, all row chunks of RT rows
 // of X: 256 (eight waves of 128 x 64), or 128 for narrow targets (R <= 128:
 // eight waves of 64 x 64, one X load task per thread).
-template <bool TRI, int DT, int RT>
+// SHARE: the chunks are shared by gridDim.y workgroups, as in k_init (its own
+// instance: with the chunks' stride in a register the triangular one takes 8.3
+// ms instead of 7.7 at m = 4096, n = 65536).
+template <bool TRI, int DT, int RT, bool SHARE>
 __global__ __launch_bounds__(kI2Threads, 1) void k_init_x3(const float *__restrict__ X,
                                                            int64_t ldx, int64_t R, AView A,
                                                            double *__restrict__ f0,
                                                            double *__restrict__ g0,
-                                                           uint8_t *__restrict__ mask0) {
+                                                           uint8_t *__restrict__ mask0,
+                                                           double *__restrict__ fp) {
   constexpr int NT = 256;
   static_assert(kI2Threads == 512, "two load tasks per operand and thread");
   static_assert(RT == 256 || (RT == 128 && !TRI), "row chunk of 256, or 128 without the triangle");
@@ -668,7 +683,7 @@ __global__ __launch_bounds__(kI2Threads, 1) void k_init_x3(const float *__restri
   uint4 yq[2];  // raw BF16 / FP8 codes: eight k of one column
 
   const int64_t nchunks = (R + RT - 1) / RT;
-  for (int64_t rc = 0; rc < nchunks; ++rc) {
+  for (int64_t rc = SHARE ? blockIdx.y : 0; rc < nchunks; rc += SHARE ? gridDim.y : 1) {
     const int64_t r0 = rc * RT;
     f32x4 acc[RBW][4];
 #pragma unroll
@@ -893,8 +908,13 @@ __global__ __launch_bounds__(kI2Threads, 1) void k_init_x3(const float *__restri
       const double fv = red[0][tid] + red[1][tid];
       const double g = ((gpart[0][tid] + gpart[1][tid]) + gpart[2][tid]) + gpart[3][tid];
       const double sc = col_scale(A, j);
-      const double f = (TRI ? 2.0 : 1.0) * sc * sc * fv;
       const double gsc = sc * sc * g;
+      if constexpr (SHARE) {
+        fp[(int64_t)blockIdx.y * n + j] = fv;
+        if (blockIdx.y == 0) g0[j] = gsc;
+        return;
+      }
+      const double f = (TRI ? 2.0 : 1.0) * sc * sc * fv;
       f0[j] = f;
       g0[j] = gsc;
       mask0[j] = (gsc > 0.0 && isfinite(gsc) && isfinite(f)) ? 0 : 2;
@@ -1653,31 +1673,50 @@ __global__ __launch_bounds__(kG2Threads, 1) void k_proj_x3(AView A, const float 
 // workgroup per 64 x 64 tile (bi <= bj) of the upper part: partial sums are
 // read along the contiguous rows, the tile is written in place and, through
 // LDS, transposed into the lower part, so every access is coalesced.
+// (64 x 16 entries per workgroup, four per thread with eight partials of each
+// in flight, added in order: with one workgroup per 64 x 64 tile and a load at
+// a time, the partials' latency made m = 1024, n = 60000 815 us, now 91 us)
+constexpr int kGrU = 8;
 __global__ __launch_bounds__(256) void k_gram_reduce(const float *__restrict__ P, int64_t ldp,
                                                      int64_t m, int nsplit,
                                                      float *__restrict__ C, int64_t ldc) {
-  __shared__ float T[64][65];
+  __shared__ float T[64][17];
   int64_t bj = 0;
   const int64_t tile = blockIdx.x;
   while ((bj + 1) * (bj + 2) / 2 <= tile) ++bj;
   const int64_t bi = tile - bj * (bj + 1) / 2;
-  const int rr = threadIdx.x & 63, c0 = threadIdx.x >> 6;
+  const int rr = threadIdx.x & 63, c0 = (threadIdx.x >> 6) * 4;
+  const int64_t x0 = bj * 64 + 16 * blockIdx.y;  // first of this workgroup's 16 columns
   const int64_t i = bi * 64 + rr;
-  for (int x = c0; x < 64; x += 4) {
-    const int64_t j = bj * 64 + x;
-    float v = 0.f;
-    if (i < m && j < m && (bi < bj || i <= j)) {
-      for (int sp = 0; sp < nsplit; ++sp) v += P[(int64_t)sp * ldp * m + j * ldp + i];
-      C[j * ldc + i] = v;
+  const int64_t ic = i < m ? i : m - 1;
+  float v[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int s0 = 0; s0 < nsplit; s0 += kGrU) {
+    float w[4][kGrU];
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      const int64_t j = x0 + c0 + x < m ? x0 + c0 + x : m - 1;
+#pragma unroll
+      for (int u = 0; u < kGrU; ++u)
+        w[x][u] = P[(int64_t)(s0 + u < nsplit ? s0 + u : nsplit - 1) * ldp * m + j * ldp + ic];
     }
-    T[rr][x] = v;
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+#pragma unroll
+      for (int u = 0; u < kGrU; ++u)
+        if (s0 + u < nsplit) v[x] += w[x][u];
+  }
+#pragma unroll
+  for (int x = 0; x < 4; ++x) {
+    const int64_t j = x0 + c0 + x;
+    if (i < m && j < m && (bi < bj || i <= j)) C[j * ldc + i] = v[x];
+    T[rr][c0 + x] = v[x];
   }
   __syncthreads();
   // lower part: C[j][i] = C[i][j] for the tile's (i, j), i < j
-  for (int x = c0; x < 64; x += 4) {
-    const int64_t ic = bi * 64 + x;   // column of the lower element
-    const int64_t jr = bj * 64 + rr;  // its row
-    if (ic < m && jr < m && ic < jr) C[ic * ldc + jr] = T[x][rr];
+  for (int e = threadIdx.x; e < 64 * 16; e += 256) {
+    const int a = e >> 4, b = e & 15;
+    const int64_t col = bi * 64 + a, row = x0 + b;  // of the lower element
+    if (col < m && row < m && col < row) C[col * ldc + row] = T[a][b];
   }
 }
 
@@ -2034,38 +2073,99 @@ static bool mfma_db() {
 }
 constexpr int KC_ALIGN = 32;  // split-K chunks are multiples of every stage depth
 
+// f0 = the sum of the ny parts of f (in order) with the column's scale, mask0.
+template <bool TRI>
+__global__ __launch_bounds__(256) void k_init_finish(AView A, const double *__restrict__ fp, int ny,
+                                                     double *__restrict__ f0,
+                                                     const double *__restrict__ g0,
+                                                     uint8_t *__restrict__ mask0) {
+  const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (j >= A.n) return;
+  double fv = 0.0;
+  for (int y = 0; y < ny; ++y) fv += fp[(int64_t)y * A.n + j];
+  const double sc = col_scale(A, j);
+  const double f = (TRI ? 2.0 : 1.0) * sc * sc * fv, g = g0[j];
+  f0[j] = f;
+  mask0[j] = (g > 0.0 && isfinite(g) && isfinite(f)) ? 0 : 2;
+}
+
+// Scratch for the shared row chunks of the initial scores.
+struct InitScratch {
+  double *fp;
+  size_t bytes;
+};
+// How many workgroups share the row chunks of `grid` column tiles: as many as
+// fill the chip's 256 CUs, no more than there are chunks or scratch for.  (m =
+// 500, n = 1000, B = A: 108 us with 16 workgroups, 21 us with 128; m = 1024,
+// n = 60000: 235 workgroups, left alone.)
+static int init_share(unsigned grid, int64_t chunks, int64_t n, const InitScratch &sc) {
+  int64_t y = 256 / (grid < 1 ? 1 : grid);
+  if (y > chunks) y = chunks;
+  while (y > 1 && (size_t)y * n * sizeof(double) > sc.bytes) --y;
+  return y < 1 ? 1 : (int)y;
+}
+template <bool TRI>
+static hipError_t init_finish(const AView &A, const InitScratch &sc, int ny, double *f0,
+                              const double *g0, uint8_t *mask0, hipStream_t s) {
+  hipError_t e = hipGetLastError();
+  if (e || ny == 1) return e;
+  hipLaunchKernelGGL((k_init_finish<TRI>), dim3((unsigned)((A.n + 255) / 256)), dim3(256), 0, s, A,
+                     (const double *)sc.fp, ny, f0, g0, mask0);
+  return hipGetLastError();
+}
+
 template <int DT, int RB, int BKT, bool TRI>
 static hipError_t init_t(const float *X, int64_t ldx, int64_t R, const AView &A, double *f0,
-                         double *g0, uint8_t *mask0, hipStream_t s) {
+                         double *g0, uint8_t *mask0, const InitScratch &sc, hipStream_t s) {
   constexpr int NB = 4;
   // two buffers only where they fit the 160 KiB of LDS
   constexpr bool kFitsDB = 2 * (64 * RB + 16 * NB) * (BKT + 4) * 4 + 8 * 1024 <= 160 * 1024;
   const unsigned grid = (unsigned)((A.n + 16 * NB - 1) / (16 * NB));
+  const int ny = init_share(grid, (R + 64 * RB - 1) / (64 * RB), A.n, sc);
+  bool done = false;
   if constexpr (kFitsDB) {
     if (mfma_db()) {
-      hipLaunchKernelGGL((k_init<DT, RB, NB, BKT, TRI, true>), dim3(grid), dim3(256), 0, s, X,
-                         ldx, R, A, f0, g0, mask0);
-      return hipGetLastError();
+      hipLaunchKernelGGL((k_init<DT, RB, NB, BKT, TRI, true>), dim3(grid, ny), dim3(256), 0, s, X,
+                         ldx, R, A, f0, g0, mask0, sc.fp);
+      done = true;
     }
   }
-  hipLaunchKernelGGL((k_init<DT, RB, NB, BKT, TRI, false>), dim3(grid), dim3(256), 0, s, X, ldx,
-                     R, A, f0, g0, mask0);
-  return hipGetLastError();
+  if (!done)
+    hipLaunchKernelGGL((k_init<DT, RB, NB, BKT, TRI, false>), dim3(grid, ny), dim3(256), 0, s, X,
+                       ldx, R, A, f0, g0, mask0, sc.fp);
+  return init_finish<TRI>(A, sc, ny, f0, g0, mask0, s);
 }
 
 template <int DT, int BKT>
 static hipError_t init_bk(const float *X, int64_t ldx, int64_t R, const AView &A, double *f0,
-                          double *g0, uint8_t *mask0, bool gram, hipStream_t s) {
-  if (gram) return init_t<DT, 4, BKT, true>(X, ldx, R, A, f0, g0, mask0, s);
-  if (R <= 64) return init_t<DT, 1, BKT, false>(X, ldx, R, A, f0, g0, mask0, s);
-  if (R <= 128) return init_t<DT, 2, BKT, false>(X, ldx, R, A, f0, g0, mask0, s);
-  if (R <= 256) return init_t<DT, 4, BKT, false>(X, ldx, R, A, f0, g0, mask0, s);
-  return init_t<DT, 8, BKT, false>(X, ldx, R, A, f0, g0, mask0, s);
+                          double *g0, uint8_t *mask0, bool gram, const InitScratch &sc, hipStream_t s) {
+  // few columns: chunks of 64 rows, so that more workgroups can share them,
+  // and deep stages, whose latency is what such a chunk costs
+  if (gram && A.n <= 64 * 64) return init_t<DT, 1, 32, true>(X, ldx, R, A, f0, g0, mask0, sc, s);
+  if (gram) return init_t<DT, 4, BKT, true>(X, ldx, R, A, f0, g0, mask0, sc, s);
+  if (R <= 64) return init_t<DT, 1, BKT, false>(X, ldx, R, A, f0, g0, mask0, sc, s);
+  if (R <= 128) return init_t<DT, 2, BKT, false>(X, ldx, R, A, f0, g0, mask0, sc, s);
+  if (R <= 256) return init_t<DT, 4, BKT, false>(X, ldx, R, A, f0, g0, mask0, sc, s);
+  return init_t<DT, 8, BKT, false>(X, ldx, R, A, f0, g0, mask0, sc, s);
+}
+
+template <bool TRI, int DT, int RT>
+static hipError_t init_x3(unsigned grid, const float *X, int64_t ldx, int64_t R, const AView &A,
+                          double *f0, double *g0, uint8_t *mask0, const InitScratch &sc,
+                          hipStream_t s) {
+  const int ny = init_share(grid, (R + RT - 1) / RT, A.n, sc);
+  if (ny > 1)
+    hipLaunchKernelGGL((k_init_x3<TRI, DT, RT, true>), dim3(grid, ny), dim3(kI2Threads), 0, s, X,
+                       ldx, R, A, f0, g0, mask0, sc.fp);
+  else
+    hipLaunchKernelGGL((k_init_x3<TRI, DT, RT, false>), dim3(grid), dim3(kI2Threads), 0, s, X, ldx,
+                       R, A, f0, g0, mask0, (double *)nullptr);
+  return init_finish<TRI>(A, sc, ny, f0, g0, mask0, s);
 }
 
 template <int DT>
 static hipError_t init_dt(const float *X, int64_t ldx, int64_t R, const AView &A, double *f0,
-                          double *g0, uint8_t *mask0, bool gram, hipStream_t s) {
+                          double *g0, uint8_t *mask0, bool gram, const InitScratch &sc, hipStream_t s) {
   // large tiles once the row dimension fills them (GCSS_MFMA_INIT256=0: off)
   static const bool big_ok = [] {
     const char *e = std::getenv("GCSS_MFMA_INIT256");
@@ -2074,21 +2174,13 @@ static hipError_t init_dt(const float *X, int64_t ldx, int64_t R, const AView &A
   // narrow targets (64 <= R <= 128) on the BF16 matrix cores: 128-row chunks
   if (big_ok && mfma_x3() && !gram && R >= 64 && R <= 128 && A.n >= 1024) {
     const unsigned grid = (unsigned)((A.n + 255) / 256);
-    hipLaunchKernelGGL((k_init_x3<false, DT, 128>), dim3(grid), dim3(kI2Threads), 0, s, X, ldx, R,
-                       A, f0, g0, mask0);
-    return hipGetLastError();
+    return init_x3<false, DT, 128>(grid, X, ldx, R, A, f0, g0, mask0, sc, s);
   }
   if (big_ok && R >= 192 && A.n >= 1024) {
     const unsigned grid = (unsigned)((A.n + 255) / 256);
-    if (mfma_x3()) {
-      if (gram)
-        hipLaunchKernelGGL((k_init_x3<true, DT, 256>), dim3(grid), dim3(kI2Threads), 0, s, X, ldx,
-                           R, A, f0, g0, mask0);
-      else
-        hipLaunchKernelGGL((k_init_x3<false, DT, 256>), dim3(grid), dim3(kI2Threads), 0, s, X, ldx,
-                           R, A, f0, g0, mask0);
-      return hipGetLastError();
-    }
+    if (mfma_x3())
+      return gram ? init_x3<true, DT, 256>(grid, X, ldx, R, A, f0, g0, mask0, sc, s)
+                  : init_x3<false, DT, 256>(grid, X, ldx, R, A, f0, g0, mask0, sc, s);
     if (gram)
       hipLaunchKernelGGL((k_init256<DT, true>), dim3(grid), dim3(kI2Threads), 0, s, X, ldx, R, A,
                          f0, g0, mask0);
@@ -2097,26 +2189,30 @@ static hipError_t init_dt(const float *X, int64_t ldx, int64_t R, const AView &A
                          f0, g0, mask0);
     return hipGetLastError();
   }
-  if (mfma_bk(gram) == 16) return init_bk<DT, 16>(X, ldx, R, A, f0, g0, mask0, gram, s);
-  return init_bk<DT, 32>(X, ldx, R, A, f0, g0, mask0, gram, s);
+  if (mfma_bk(gram) == 16) return init_bk<DT, 16>(X, ldx, R, A, f0, g0, mask0, gram, sc, s);
+  return init_bk<DT, 32>(X, ldx, R, A, f0, g0, mask0, gram, sc, s);
 }
 
 hipError_t launch_init_factor(const float *X, int64_t ldx, int64_t R, const AView &A,
-                              double *f0, double *g0, uint8_t *mask0, hipStream_t s) {
+                              double *f0, double *g0, uint8_t *mask0, void *scratch,
+                              size_t scratch_bytes, hipStream_t s) {
+  const InitScratch sc{(double *)scratch, scratch_bytes};
   switch (A.dtype) {
-    case DT_F32: return init_dt<DT_F32>(X, ldx, R, A, f0, g0, mask0, false, s);
-    case DT_BF16: return init_dt<DT_BF16>(X, ldx, R, A, f0, g0, mask0, false, s);
-    case DT_FP8: return init_dt<DT_FP8>(X, ldx, R, A, f0, g0, mask0, false, s);
+    case DT_F32: return init_dt<DT_F32>(X, ldx, R, A, f0, g0, mask0, false, sc, s);
+    case DT_BF16: return init_dt<DT_BF16>(X, ldx, R, A, f0, g0, mask0, false, sc, s);
+    case DT_FP8: return init_dt<DT_FP8>(X, ldx, R, A, f0, g0, mask0, false, sc, s);
   }
   return hipErrorInvalidValue;
 }
 
 hipError_t launch_init_gram(const float *C, int64_t ldc, const AView &A, double *f0,
-                            double *g0, uint8_t *mask0, hipStream_t s) {
+                            double *g0, uint8_t *mask0, void *scratch, size_t scratch_bytes,
+                            hipStream_t s) {
+  const InitScratch sc{(double *)scratch, scratch_bytes};
   switch (A.dtype) {
-    case DT_F32: return init_dt<DT_F32>(C, ldc, A.m, A, f0, g0, mask0, true, s);
-    case DT_BF16: return init_dt<DT_BF16>(C, ldc, A.m, A, f0, g0, mask0, true, s);
-    case DT_FP8: return init_dt<DT_FP8>(C, ldc, A.m, A, f0, g0, mask0, true, s);
+    case DT_F32: return init_dt<DT_F32>(C, ldc, A.m, A, f0, g0, mask0, true, sc, s);
+    case DT_BF16: return init_dt<DT_BF16>(C, ldc, A.m, A, f0, g0, mask0, true, sc, s);
+    case DT_FP8: return init_dt<DT_FP8>(C, ldc, A.m, A, f0, g0, mask0, true, sc, s);
   }
   return hipErrorInvalidValue;
 }
@@ -2234,7 +2330,7 @@ hipError_t launch_gram(const AView &A, float *C, int64_t ldc, void *scratch, int
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int64_t nb64 = (A.m + 63) / 64;
-  hipLaunchKernelGGL(k_gram_reduce, dim3((unsigned)(nb64 * (nb64 + 1) / 2)), dim3(256), 0, s, P,
+  hipLaunchKernelGGL(k_gram_reduce, dim3((unsigned)(nb64 * (nb64 + 1) / 2), 4), dim3(256), 0, s, P,
                      ldp, A.m, sp, C, ldc);
   return hipGetLastError();
 }
