@@ -289,6 +289,7 @@ struct gcss_ctx {
   float *history() const { return use_chain && L.hist ? at<float>(L.wh) : nullptr; }
   double *F0() const { return at<double>(L.scal); }
   double *err_dev() const { return at<double>(L.scal) + 1; }
+  int *basis_flag() const { return (int *)(at<double>(L.scal) + 2); }  // read with the error
 };
 
 namespace {
@@ -920,14 +921,8 @@ gcss_status gcss_reconstruction_error(gcss_ctx *h, const int64_t *idx, int32_t k
                                  h->at<double>(h->L.f), h->at<double>(h->L.g), h->at<uint8_t>(h->L.mask),
                                  h->d.n, sb, k, h->d.k_max, h->F0(), kBasisTau, s));
       if (block) {
-        HIPCHK(launch_basis(bp, h->at<char>(h->L.scratch), h->A, pick, k, h->at<double>(h->L.Q), ldq, sb.st, s));
-        int bad = 0;
-        HIPCHK(hipMemcpyAsync(&bad, h->at<char>(h->L.scratch) + bp.flag, sizeof bad, hipMemcpyDeviceToHost, s));
-        HIPCHK(hipStreamSynchronize(s));
-        if (bad) {
-          block = false;
-          continue;
-        }
+        HIPCHK(launch_basis(bp, h->at<char>(h->L.scratch), h->A, pick, k, h->at<double>(h->L.Q), ldq, sb.st,
+                            h->basis_flag(), s));
       } else {
         for (int i = 0; i < k; ++i) HIPCHK(enqueue_basis_step(h, sb));
         DevState hs;
@@ -936,25 +931,34 @@ gcss_status gcss_reconstruction_error(gcss_ctx *h, const int64_t *idx, int32_t k
         kb = hs.t;
       }
     }
-    break;
+    const double *Q = h->at<double>(h->L.Q);
+    char *scr = h->at<char>(h->L.scratch);
+    if (h->target == 1) {
+      HIPCHK(launch_err_tiled(Q, ldq, m, kb, h->B, h->ldb, h->r, scr, h->L.scratch_bytes, h->num_cu,
+                              h->err_dev(), s));
+    } else if (kb == 0) {
+      HIPCHK(launch_sum_f64(h->F0(), 1, h->err_dev(), nullptr, 0, s));
+    } else {
+      // ||A||^2 - sum_s ||A^T q_s||^2; the selection that built this basis
+      // already computed the terms exactly (quad), so only a fresh basis needs them
+      double *quad = h->at<double>(h->L.quad);
+      if (!reuse) HIPCHK(launch_qta(Q, ldq, kb, nullptr, h->A, (double *)scr, quad, s));
+      HIPCHK(launch_gram_err(h->F0(), quad, kb, h->err_dev(), s));
+    }
+    // the error and, beside it, whether its basis stands (an uncertified one
+    // may hold anything: its error is dropped)
+    double res[2] = {0.0, 0.0};
+    HIPCHK(hipMemcpyAsync(res, h->err_dev(), sizeof res, hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    int bad;
+    memcpy(&bad, &res[1], sizeof bad);
+    if (block && bad) {
+      block = false;
+      continue;
+    }
+    *err = res[0];
+    return GCSS_OK;
   }
-  const double *Q = h->at<double>(h->L.Q);
-  char *scr = h->at<char>(h->L.scratch);
-  if (h->target == 1) {
-    HIPCHK(launch_err_tiled(Q, ldq, m, kb, h->B, h->ldb, h->r, scr, h->L.scratch_bytes, h->num_cu,
-                            h->err_dev(), s));
-  } else if (kb == 0) {
-    HIPCHK(launch_sum_f64(h->F0(), 1, h->err_dev(), nullptr, 0, s));
-  } else {
-    // ||A||^2 - sum_s ||A^T q_s||^2; the selection that built this basis
-    // already computed the terms exactly (quad), so only a fresh basis needs them
-    double *quad = h->at<double>(h->L.quad);
-    if (!reuse) HIPCHK(launch_qta(Q, ldq, kb, nullptr, h->A, (double *)scr, quad, s));
-    HIPCHK(launch_gram_err(h->F0(), quad, kb, h->err_dev(), s));
-  }
-  HIPCHK(hipMemcpyAsync(err, h->err_dev(), sizeof(double), hipMemcpyDeviceToHost, s));
-  HIPCHK(hipStreamSynchronize(s));
-  return GCSS_OK;
 }
 
 gcss_status gcss_set_embedding(gcss_ctx *h, float *w, int64_t ldw) {

@@ -249,14 +249,14 @@ hipError_t launch_chain_block(const ChainArgs &ca, hipStream_t s);
 struct BasisPlan {
   int nsplit;
   int64_t rows;  // per split
-  size_t S, Y, part, W, flag, bytes;
+  size_t S, Y, part, W, bytes;
 };
 BasisPlan basis_plan(int64_t m, int64_t ldq, int kmax);
 // Q[:, 0..k) = an orthonormal basis of the columns pick[0..k) of A, in their
-// order, state t = k; the int at scr + P.flag is 1 where it is not certified
-// (the caller then runs Gram-Schmidt), else 0
+// order, state t = k; *flag is 1 where it is not certified (the caller then
+// runs Gram-Schmidt), else 0
 hipError_t launch_basis(const BasisPlan &P, char *scr, const AView &A, const int64_t *pick, int k,
-                        double *Q, int64_t ldq, DevState *st, hipStream_t s);
+                        double *Q, int64_t ldq, DevState *st, int *flag, hipStream_t s);
 
 // ---- launchers (k_mfma.hip) ----
 // (scratch: parts of f where few columns share their rows' chunks)

@@ -3,7 +3,7 @@
 // A selection builds its basis one column at a time because each pick waits
 // for the scores before it; the columns of a caller's subset are all known,
 // so their basis needs no serial Gram-Schmidt (four launches and two
-// reductions per column).  A subset of 100 columns at m = 1024 takes 0.23 ms
+// reductions per column).  A subset of 100 columns at m = 1024 takes 0.19 ms
 // with the error, against 2.06 ms column by column (MI355X).  Cholesky QR, in
 // chunks of kBC columns:
 //
@@ -146,79 +146,86 @@ __global__ __launch_bounds__(256) void k_bs_reduce(const double *__restrict__ pa
   }
 }
 
-// out = X W (sub 0) or in - X W (sub 1), 64 x 64 tile of rows 64 x.. and
-// columns 64 y..: X has kx columns (a multiple of kBK is read: W's rows past
-// kx are zero, X's columns are clamped), W is row-major with kBC columns.
-// Only columns < b and rows < m are written.  st: the state of a finished
-// basis of k columns (last chunk).
+// out = X W, or in - X W, for the 32 x 64 tile of rows 32 x.. and columns 64
+// y..: X has kx columns, W is row-major with kBC columns.  Only columns < b and
+// rows < m are written.  st: the state of a finished basis of k columns (last
+// chunk).  A FP64 matrix instruction takes 64 cycles of a SIMD, so the tile is
+// kept low (twice the workgroups), and the next chunk's loads are in flight
+// while this one is multiplied: 12.0 -> 7.5 us at m = 1024.
+constexpr int kBR = 32;
 __global__ __launch_bounds__(256) void k_bs_nn(const double *__restrict__ X, int kx,
                                                const double *__restrict__ W,
                                                const double *__restrict__ in, double *out,
                                                int64_t ldq, int64_t m, int b, DevState *st, int k) {
-  constexpr int P = kBT + 16;  // LDS pitch: four rows of 16 doubles, conflict-free
-  __shared__ double xs[kBK * P];  // [k][row]
-  __shared__ double ws[kBK * P];  // [k][column]
+  constexpr int PX = kBR + 16, PW = kBT + 16;  // LDS pitches: four rows of 16 doubles, conflict-free
+  __shared__ double xs[kBK * PX];  // [k][row]
+  __shared__ double ws[kBK * PW];  // [k][column]
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t j0 = (int64_t)blockIdx.x * kBT;
+  const int64_t j0 = (int64_t)blockIdx.x * kBR;
   const int c0 = blockIdx.y * kBT;
-  const int wi = (wave >> 1) * 32, wj = (wave & 1) * 32, i16 = lane & 15, kg = lane >> 4;
-  const int lr = 2 * (threadIdx.x & 31), lk = threadIdx.x >> 5;  // loader: 64 wide x 8 at a time
-  f64x4 acc[2][2] = {};
-  for (int k0 = 0; k0 < kx; k0 += kBK) {
-    double2 xv[4], wv[4];
+  const int wi = (wave >> 1) * 16, wj = (wave & 1) * 32, i16 = lane & 15, kg = lane >> 4;
+  const int xr = 2 * (threadIdx.x & 15), xk = threadIdx.x >> 4;  // loader of X: 32 rows x 16 at a time
+  const int lr = 2 * (threadIdx.x & 31), lk = threadIdx.x >> 5;  // of W: 64 columns x 8 at a time
+  f64x4 acc[2] = {};
+  double2 xv[2], wv[4];
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int kk = k0 + xk + 16 * u;
+      xv[u] = *(const double2 *)(X + (int64_t)(kk < kx ? kk : kx - 1) * ldq + j0 + xr);
+    }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int kk = k0 + lk + 8 * u, kc = kk < kx ? kk : kx - 1;
-      xv[u] = *(const double2 *)(X + (int64_t)kc * ldq + j0 + lr);
-      wv[u] = *(const double2 *)(W + (int64_t)kc * kBC + c0 + lr);
+      const int kk = k0 + lk + 8 * u;
+      wv[u] = *(const double2 *)(W + (int64_t)(kk < kx ? kk : kx - 1) * kBC + c0 + lr);
+    }
+  };
+  load(0);
+  for (int k0 = 0; k0 < kx; k0 += kBK) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int kk = xk + 16 * u;
+      const bool ok = k0 + kk < kx;
+      xs[kk * PX + xr] = ok && j0 + xr < m ? xv[u].x : 0.0;
+      xs[kk * PX + xr + 1] = ok && j0 + xr + 1 < m ? xv[u].y : 0.0;
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int kk = lk + 8 * u;
       const bool ok = k0 + kk < kx;
-      xs[kk * P + lr] = ok && j0 + lr < m ? xv[u].x : 0.0;
-      xs[kk * P + lr + 1] = ok && j0 + lr + 1 < m ? xv[u].y : 0.0;
-      ws[kk * P + lr] = ok ? wv[u].x : 0.0;
-      ws[kk * P + lr + 1] = ok ? wv[u].y : 0.0;
+      ws[kk * PW + lr] = ok ? wv[u].x : 0.0;
+      ws[kk * PW + lr + 1] = ok ? wv[u].y : 0.0;
     }
     __syncthreads();
+    if (k0 + kBK < kx) load(k0 + kBK);
 #pragma unroll
     for (int s = 0; s < kBK / 4; ++s) {
-      double xa[2], wb[2];
+      const double xa = xs[(4 * s + kg) * PX + wi + i16];
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        xa[h] = xs[(4 * s + kg) * P + wi + 16 * h + i16];
-        wb[h] = ws[(4 * s + kg) * P + wj + 16 * h + i16];
-      }
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int c = 0; c < 2; ++c) acc[a][c] = mfma64(xa[a], wb[c], acc[a][c]);
+      for (int c = 0; c < 2; ++c) acc[c] = mfma64(xa, ws[(4 * s + kg) * PW + wj + 16 * c + i16], acc[c]);
     }
     __syncthreads();
   }
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int c = 0; c < 2; ++c)
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        // (register v holds row kg + 4 v of the tile, column i16)
-        const int64_t j = j0 + wi + 16 * a + kg + 4 * v;
-        const int col = c0 + wj + 16 * c + i16;
-        if (j < m && col < b) {
-          const int64_t o = (int64_t)col * ldq + j;
-          out[o] = in ? in[o] - acc[a][c][v] : acc[a][c][v];
-        }
+    for (int v = 0; v < 4; ++v) {
+      // (register v holds row kg + 4 v of the tile, column i16)
+      const int64_t j = j0 + wi + kg + 4 * v;
+      const int col = c0 + wj + 16 * c + i16;
+      if (j < m && col < b) {
+        const int64_t o = (int64_t)col * ldq + j;
+        out[o] = in ? in[o] - acc[c][v] : acc[c][v];
       }
+    }
   if (st && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
     st->t = k;
     st->pos = k;
   }
 }
 
-// T = R^-1 (row-major kBC x kBC, upper; identity past b) with R^T R = the sum
-// of the Gram tiles, by one workgroup with the matrix in LDS: L = R^T by
+// T = R^-1 (row-major kBC x kBC, upper; identity past b) with R^T R = the Gram
+// matrix, by one workgroup with the matrix in LDS: L = R^T by
 // panels of 16 (one wave factors and inverts the 16 x 16 diagonal block, the
 // rows below are multiplied by that inverse, the trailing matrix is updated
 // on the matrix cores), then L^-1 from the blocks' inverses by doubling
@@ -250,39 +257,27 @@ __device__ __forceinline__ void tile_store(double *o, const f64x4 &v) {
 }
 
 // v of lane x (a constant), in scalar registers: shuffles (an LDS round trip
-// per broadcast), FP64 roots and divisions made the kernel 175 us, now 74 us
+// per broadcast), FP64 roots and divisions made the kernel 175 us, now 63 us
 __device__ __forceinline__ double lane_value(double v, int x) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), x),
                           __builtin_amdgcn_readlane(__double2loint(v), x));
 }
 
-__global__ __launch_bounds__(kCThreads) void k_bs_chol(const double *__restrict__ part, int nsplit,
-                                                       int b, double *__restrict__ T,
+__global__ __launch_bounds__(kCThreads) void k_bs_chol(const double *__restrict__ gram, int b,
+                                                       double *__restrict__ T,
                                                        int *__restrict__ flag) {
   __shared__ double G[kBC * kCP];
   __shared__ double D[kBC * 16];  // inverses of the diagonal blocks, row-major 16 x 16 each
   __shared__ double g0[kBC];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  // the Gram matrix, identity past b
-  constexpr int nty = kBC / kBT;
-  for (int e0 = threadIdx.x; e0 < kBC * kBC; e0 += 4 * kCThreads) {
-    double s[4] = {0.0, 0.0, 0.0, 0.0};
-    const double *src[4];
+  // the Gram matrix, identity past b (gram and T may be one buffer)
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int e = e0 + u * kCThreads, i = e / kBC, j = e % kBC;
-      src[u] = part + ((int64_t)(i / kBT) * nty + j / kBT) * kBT * kBT + (i % kBT) * kBT + j % kBT;
-    }
-    for (int z = 0; z < nsplit; ++z)
-#pragma unroll
-      for (int u = 0; u < 4; ++u) s[u] += src[u][(int64_t)z * nty * nty * kBT * kBT];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int e = e0 + u * kCThreads, i = e / kBC, j = e % kBC;
-      if (i >= b || j >= b) s[u] = i == j ? 1.0 : 0.0;
-      G[i * kCP + j] = s[u];
-      if (i == j) g0[i] = s[u];
-    }
+  for (int u = 0; u < kBC * kBC / kCThreads; ++u) {
+    const int e = threadIdx.x + u * kCThreads, i = e / kBC, j = e % kBC;
+    double s = gram[e];
+    if (i >= b || j >= b) s = i == j ? 1.0 : 0.0;
+    G[i * kCP + j] = s;
+    if (i == j) g0[i] = s;
   }
   __syncthreads();
   bool bad = false;
@@ -405,8 +400,8 @@ __global__ __launch_bounds__(kCThreads) void k_bs_chol(const double *__restrict_
 
 BasisPlan basis_plan(int64_t m, int64_t ldq, int kmax) {
   BasisPlan P{};
-  // row splits of about 128 rows while that makes no more than 16
-  P.nsplit = (int)(m / 128 < 1 ? 1 : m / 128 > 16 ? 16 : m / 128);
+  // row splits of about 64 rows while that makes no more than 32
+  P.nsplit = (int)(m / 64 < 1 ? 1 : m / 64 > 32 ? 32 : m / 64);
   P.rows = ((m + P.nsplit - 1) / P.nsplit + kBK - 1) / kBK * kBK;
   P.nsplit = (int)((m + P.rows - 1) / P.rows);
   const int ntx = (kmax + kBT - 1) / kBT;
@@ -421,18 +416,16 @@ BasisPlan basis_plan(int64_t m, int64_t ldq, int kmax) {
   P.Y = take((size_t)ldq * kBC * 8);
   P.part = take((size_t)P.nsplit * tiles * kBT * kBT * 8);
   P.W = take((size_t)(ntx > 2 ? ntx : 2) * kBT * kBC * 8);
-  P.flag = take(256);
   P.bytes = off;
   return P;
 }
 
 hipError_t launch_basis(const BasisPlan &P, char *scr, const AView &A, const int64_t *pick, int k,
-                        double *Q, int64_t ldq, DevState *st, hipStream_t s) {
+                        double *Q, int64_t ldq, DevState *st, int *flag, hipStream_t s) {
   const int64_t m = A.m;
   double *S = (double *)(scr + P.S), *Y = (double *)(scr + P.Y), *part = (double *)(scr + P.part),
          *W = (double *)(scr + P.W);
-  int *flag = (int *)(scr + P.flag);
-  const unsigned nr = (unsigned)((m + kBT - 1) / kBT), ns = (unsigned)P.nsplit;
+  const unsigned nr = (unsigned)((m + kBR - 1) / kBR), ns = (unsigned)P.nsplit;
   auto tn = [&](const double *X, int nx, const double *Z) {
     hipLaunchKernelGGL(k_bs_tn, dim3((unsigned)((nx + kBT - 1) / kBT), kBC / kBT, ns), dim3(256), 0, s,
                        X, nx, Z, ldq, m, P.rows, part);
@@ -456,7 +449,8 @@ hipError_t launch_basis(const BasisPlan &P, char *scr, const AView &A, const int
       nn(Q, t0, S, S, kBC, nullptr);
     }
     tn(S, kBC, S);
-    hipLaunchKernelGGL(k_bs_chol, dim3(1), dim3(kCThreads), 0, s, part, P.nsplit, b, W, flag);
+    reduce(kBC, 0, b);
+    hipLaunchKernelGGL(k_bs_chol, dim3(1), dim3(kCThreads), 0, s, W, b, W, flag);
     nn(S, kBC, nullptr, Y, kBC, nullptr);
     if (t0 > 0) {
       tn(Q, t0, Y);
