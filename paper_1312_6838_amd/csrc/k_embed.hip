@@ -208,15 +208,16 @@ __global__ __launch_bounds__(256) void k_jac_floor(const double *__restrict__ G,
 // Within an inner round the 32 rotations touch disjoint index pairs, so
 // S <- J^T S J splits into independent 2 x 2 blocks.
 //
-// Bound by the inner rounds' latency and LDS traffic.  1024 threads take one
-// 2 x 2 block of S each; while wave 0 forms the next round's rotations from
-// S, the other waves apply this round's to V, which is kept by columns so
-// that a wave's 64 rows are consecutive words.  The rotation's tangent is
-// taken in binary32 (V only has to be orthogonal, so c and s are normalised
-// in FP64; a tangent off by 1e-7 leaves 1e-7 of the entry, which later
-// rotations see).  An inner round took 1.7 us with 256 threads, the indices
-// in LDS, FP64 roots and divisions and V updated before the next rotations;
-// now 1.2 us (a solve of round 0: 107 -> 81 us, of another round: 43 us).
+// Bound by the inner rounds' latency and LDS traffic.  S is kept as its lower
+// triangle, whose 528 blocks of 2 x 2 are one per thread of nine waves; the
+// other waves apply the round's rotations to part of V meanwhile, and all but
+// wave 0 to the rest while that forms the next rotations from S.  V is kept by
+// columns, so that a wave's 64 rows are consecutive words.  The rotation's
+// tangent is taken in binary32 (V only has to be orthogonal, so c and s are
+// normalised in FP64; a tangent off by 1e-7 leaves 1e-7 of the entry, which
+// later rotations see).  An inner round took 1.7 us with 256 threads, the
+// indices in LDS, FP64 roots and divisions and V updated before the next
+// rotations; now 1.1 us (a solve of round 0: 107 -> 73 us, of another: 41 us).
 constexpr int kJacThreads = 1024;
 
 __device__ __forceinline__ void jac_inner_pair(bool full, int rr, int p, int &x, int &y) {
@@ -245,6 +246,13 @@ __device__ __forceinline__ void jac_idx(bool full, int p, JacIdx &x, JacIdx &y) 
   if (x.step == 0) x.end = -1;
   y = {b, 1, full ? kJP - 1 : kJP, full ? 0 : kJB};
 }
+
+// S is kept as its lower triangle: element (i, j) of the symmetric matrix.
+__device__ __forceinline__ double *jac_low(double (*S)[kJLd], int i, int j) {
+  return i > j ? &S[i][j] : &S[j][i];
+}
+constexpr int kJacSWaves = (kJB * (kJB + 1) / 2 + 63) / 64;  // waves that hold blocks of S: 9
+constexpr int kJacVFirst = 14;  // pairs of V the other 7 waves take meanwhile
 
 __global__ __launch_bounds__(kJacThreads) void k_jac_solve(const double *__restrict__ G, int L,
                                                            int r, const double *__restrict__ aux,
@@ -279,19 +287,27 @@ __global__ __launch_bounds__(kJacThreads) void k_jac_solve(const double *__restr
   }
   __syncthreads();
   const int nrounds = busy ? (full ? kJP - 1 : kJB) : 0;
-  const int P = threadIdx.x >> 5, Q = threadIdx.x & 31;  // this thread's block of S
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // this thread's block of S, row pair P >= column pair Q (the first 528 threads)
+  int P = 0, Q = 0;
+  if (wave < kJacSWaves) {
+    P = (int)((sqrtf(8.f * threadIdx.x + 1.f) - 1.f) * 0.5f);
+    if (P * (P + 1) / 2 > (int)threadIdx.x) --P;
+    if ((P + 1) * (P + 2) / 2 <= (int)threadIdx.x) ++P;
+    Q = threadIdx.x - P * (P + 1) / 2;
+  }
+  const bool sact = threadIdx.x < kJB * (kJB + 1) / 2;
   JacIdx x0, y0, x1, y1, xr, yr;
-  jac_idx(full, P, x0, y0);
+  jac_idx(full, P & (kJB - 1), x0, y0);
   jac_idx(full, Q, x1, y1);
-  jac_idx(full, Q, xr, yr);
+  jac_idx(full, lane & (kJB - 1), xr, yr);
   // wave 0: the rotations of inner round rr, one pair per lane (pair = lane)
   auto rotations = [&](int rr) {
     bool rot = false;
     if (lane < kJB) {
       const int x = xr.v, y = yr.v;
-      const double gxx = S[x][x], gyy = S[y][y], gxy = S[x][y];
+      const double gxx = S[x][x], gyy = S[y][y], gxy = S[x > y ? x : y][x > y ? y : x];
       double c = 1.0, sv = 0.0;
       rot = !negligible(gxy, gxx, gyy, fl);
       if (rot) {
@@ -314,22 +330,37 @@ __global__ __launch_bounds__(kJacThreads) void k_jac_solve(const double *__restr
     xr.next();
     yr.next();
   };
+  // V <- V J for the pairs q0, q0 + step, ... < q1: one row per lane
+  auto v_update = [&](int rr, const double2 *J, int q0, int q1, int step) {
+    for (int q = q0; q < q1; q += step) {
+      int x, y;
+      jac_inner_pair(full, rr, q, x, y);
+      const double2 c = J[q];
+      const double va = V[x][lane], vc = V[y][lane];
+      V[x][lane] = c.x * va - c.y * vc;
+      V[y][lane] = c.y * va + c.x * vc;
+    }
+  };
   if (nrounds && wave == 0) rotations(0);
   __syncthreads();
   for (int rr = 0; rr < nrounds; ++rr) {
     const double2 *const J = cs[rr & 1];
     const bool any = nrot[rr & 1] != 0;
-    if (any) {
-      // S <- J^T S J by 2 x 2 blocks (row pair P, column pair Q)
+    if (any && sact) {
+      // S <- J^T S J by 2 x 2 blocks (row pair P, column pair Q), in the lower
+      // triangle; the diagonal blocks' two equal entries are one
       const double2 cp = J[P], cq = J[Q];
-      double *const sx = S[x0.v], *const sy = S[y0.v];
-      const double a00 = sx[x1.v], a01 = sx[y1.v], a10 = sy[x1.v], a11 = sy[y1.v];
+      double *const e00 = jac_low(S, x0.v, x1.v), *const e01 = jac_low(S, x0.v, y1.v);
+      double *const e10 = jac_low(S, y0.v, x1.v), *const e11 = jac_low(S, y0.v, y1.v);
+      const double a00 = *e00, a01 = *e01, a10 = *e10, a11 = *e11;
       const double r00 = cp.x * a00 - cp.y * a10, r01 = cp.x * a01 - cp.y * a11;
       const double r10 = cp.y * a00 + cp.x * a10, r11 = cp.y * a01 + cp.x * a11;
-      sx[x1.v] = cq.x * r00 - cq.y * r01;
-      sx[y1.v] = cq.y * r00 + cq.x * r01;
-      sy[x1.v] = cq.x * r10 - cq.y * r11;
-      sy[y1.v] = cq.y * r10 + cq.x * r11;
+      *e00 = cq.x * r00 - cq.y * r01;
+      *e01 = cq.y * r00 + cq.x * r01;
+      if (P != Q) *e10 = cq.x * r10 - cq.y * r11;
+      *e11 = cq.y * r10 + cq.x * r11;
+    } else if (any && wave >= kJacSWaves) {
+      v_update(rr, J, wave - kJacSWaves, kJacVFirst, kJacThreads / 64 - kJacSWaves);
     }
     x0.next();
     y0.next();
@@ -339,15 +370,7 @@ __global__ __launch_bounds__(kJacThreads) void k_jac_solve(const double *__restr
     if (wave == 0) {
       if (rr + 1 < nrounds) rotations(rr + 1);
     } else if (any) {
-      // V <- V J: one row per lane, pairs wave - 1, wave + 14, ...
-      for (int q = wave - 1; q < kJB; q += kJacThreads / 64 - 1) {
-        int x, y;
-        jac_inner_pair(full, rr, q, x, y);
-        const double2 c = J[q];
-        const double va = V[x][lane], vc = V[y][lane];
-        V[x][lane] = c.x * va - c.y * vc;
-        V[y][lane] = c.y * va + c.x * vc;
-      }
+      v_update(rr, J, kJacVFirst + wave - 1, kJB, kJacThreads / 64 - 1);
     }
     __syncthreads();
   }
