@@ -889,6 +889,129 @@ __global__ __launch_bounds__(kBlkThreads) void k_chain_block(ChainArgs ca) {
   }
 }
 
+// The same for one problem with the history of omega (a small explicit target):
+// the pick from the pass's winners, the column decoded here, c1 gathered.  One
+// launch instead of the slab form's three, each of which spends most of its
+// 5-8 us on its start, its first loads and its end.
+template <typename TB>
+__global__ __launch_bounds__(kBlkThreads) void k_chain_one(ChainArgs ca, AView A) {
+  extern __shared__ double lds[];  // vec (m), coefficients (kmax + 1), upsilon (r)
+  __shared__ double wsum[kBlkWaves];
+  __shared__ double bs[kBlkWaves];
+  __shared__ int64_t bi[kBlkWaves];
+  DevState *st = ca.st;
+  if (st->done) {
+    if (threadIdx.x == 0) st->dec_pending = 0;  // the pass after the last pick has run
+    return;
+  }
+  const int t = st->t;
+  const int64_t m = ca.m;
+  const int r = (int)ca.r;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const double *Q = ca.Q;
+  const TB *B = (const TB *)ca.B;
+  double *vec = lds, *cf = lds + m, *ups = cf + (ca.kmax + 1);
+  double best = -INFINITY;
+  int64_t p = kNoIdx;
+  for (int x = threadIdx.x; x < ca.npart; x += kBlkThreads) {
+    const double sc = ca.part[x].score;
+    const int64_t i = ca.part[x].idx;
+    if (better(sc, i, best, p)) {
+      best = sc;
+      p = i;
+    }
+  }
+  const int nw = ca.npart < kBlkThreads ? (ca.npart + 63) >> 6 : kBlkWaves;
+  if (wave < nw) {
+    wave_argmax(best, p);
+    if (lane == 0) {
+      bs[wave] = best;
+      bi[wave] = p;
+    }
+  }
+  __syncthreads();
+  best = bs[0];
+  p = bi[0];
+  for (int x = 1; x < nw; ++x)
+    if (better(bs[x], bi[x], best, p)) {
+      best = bs[x];
+      p = bi[x];
+    }
+  // (every thread has read the state)
+  if (threadIdx.x == 0) {
+    st->skip = 0;
+    st->dec_pending = 0;
+    st->p = p == kNoIdx ? -1 : p;
+    if (p == kNoIdx) st->exhausted = st->done = 1;
+  }
+  if (p == kNoIdx) return;
+  const double ps = col_scale(A, p);
+  for (int64_t j = threadIdx.x; j < m; j += kBlkThreads) vec[j] = ps * (double)load_elem(A, p, j);
+  for (int s = threadIdx.x; s < t; s += kBlkThreads) cf[s] = (double)ca.wh[(int64_t)s * ca.ldw + p];
+  __syncthreads();
+  // vec <- vec - Q c1, then once more with c2 = Q^T vec
+  double nrm2 = 0.0;
+  for (int pass = 0; pass < 2; ++pass) {
+    if (pass == 1) {
+      blk_dots(Q, ca.ldq, t, vec, m, cf);
+      __syncthreads();
+    }
+    double sq = 0.0;
+    for (int64_t j = threadIdx.x; j < m; j += kBlkThreads) {
+      const double e = vec[j] - blk_row(Q, ca.ldq, t, j, cf);
+      vec[j] = e;
+      sq = fma(e, e, sq);
+    }
+    __syncthreads();
+    if (pass == 1) nrm2 = blk_sum(sq, wsum);
+  }
+  const double thr = st->tau * ca.g0[p];
+  if (!(isfinite(nrm2) && nrm2 > thr)) {
+    if (threadIdx.x == 0) {
+      ca.mask[p] = 2;
+      st->skip = 1;
+      st->n_reject += 1;
+      st->enorm2 = nrm2;
+    }
+    return;
+  }
+  const double inv = 1.0 / sqrt(nrm2);
+  for (int64_t j = threadIdx.x; j < m; j += kBlkThreads) {
+    const double qv = vec[j] * inv;
+    vec[j] = qv;
+    ca.Q[(int64_t)t * ca.ldq + j] = qv;
+    ca.q64[j] = qv;
+    ca.q32[j] = (float)qv;
+  }
+  __syncthreads();
+  blk_dots(B, ca.ldb, r, vec, m, ups);
+  blk_dots((const double *)ca.V, ca.ldq, t, vec, m, cf);
+  __syncthreads();
+  for (int64_t j = threadIdx.x; j < m; j += kBlkThreads) {
+    const double wj = blk_row(B, ca.ldb, r, j, ups);
+    const double qc = blk_row(Q, ca.ldq, t, j, cf);
+    ca.V[(int64_t)t * ca.ldq + j] = wj;
+    ca.z32[j] = (float)(wj - qc);
+  }
+  if (wave == kBlkWaves - 1) {
+    double a2 = 0.0;
+    for (int c = lane; c < r; c += 64) a2 = fma(ups[c], ups[c], a2);
+    const double u2 = wave_sum(a2);
+    if (lane == 0) {
+      const double F = st->F - u2;
+      st->u2 = u2;
+      st->enorm2 = nrm2;
+      st->F = F;
+      ca.obj[t + 1] = F;
+      ca.idx[t] = p;
+      ca.mask[p] = 1;
+      st->t = t + 1;
+      st->dec_pending = 1;
+      if (t + 1 >= st->k) st->done = 1;
+    }
+  }
+}
+
 size_t chain_block_lds_bytes(int64_t m, int64_t r, int kmax) {
   return (size_t)(m + kmax + 1 + r) * sizeof(double);
 }
@@ -928,6 +1051,16 @@ bool chain_slab_fits(int64_t m, int64_t r, int kmax) {
          (int64_t)chain_row_groups(m) * (r + kmax) * (int64_t)sizeof(double) <= kSlabBytes;
 }
 
+// One workgroup does the step of a small explicit target.  Its own work grows
+// with m (r + 4 k), on one CU; the slab form's three launches cost about the same
+// at any such size.  Per step with the pass, n = 5 000, slab form -> this: m 120,
+// r 20, k 25: 27.7 -> 24.1 us; 333, 50, 25: 28.9 -> 26.4; 500, 20, 25: 29.8 ->
+// 26.2; even at 512, 128, 25 (31.1 -> 31.5), and behind at k 60 (333, 50: 27.7 ->
+// 29.4) and at 512, 128, 64 (29.5 -> 35.2).
+static bool chain_one_fits(int64_t m, int64_t r, int kmax, bool gram) {
+  return !gram && m <= 512 && r <= 64 && kmax <= 32;
+}
+
 // f(U) with U the smallest of 4, 8, 16 that holds n columns in one round
 template <typename F>
 static void with_row_u(int64_t n, F f) {
@@ -943,6 +1076,14 @@ hipError_t launch_chain(const ChainArgs &ca, hipStream_t s) {
   const unsigned qdots = (unsigned)dots_col_blocks(0, ca.kmax);
   const size_t lds_t = (size_t)(ca.kmax + 1) * sizeof(double);
   const unsigned np = (unsigned)(ca.nprob > 0 ? ca.nprob : 1);
+  if (ca.wh && chain_one_fits(m, ca.r, ca.kmax, ca.gram)) {
+    const size_t lds = chain_block_lds_bytes(m, ca.r, ca.kmax);
+    if (ca.b_bf16)
+      hipLaunchKernelGGL((k_chain_one<uint16_t>), dim3(1), dim3(kBlkThreads), lds, s, ca, *ca.A);
+    else
+      hipLaunchKernelGGL((k_chain_one<float>), dim3(1), dim3(kBlkThreads), lds, s, ca, *ca.A);
+    return hipGetLastError();
+  }
   const dim3 gr(nrg, 1, np), br(kRowThreads);
   const bool bf = ca.b_bf16 && !ca.gram;
   // the slab form takes one problem with the history of omega; B = A keeps K5
