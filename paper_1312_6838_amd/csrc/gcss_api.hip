@@ -174,12 +174,15 @@ bool make_layout_with(const gcss_desc *d, int num_cu, bool hist, bool basis, Lay
 // Two parts of the workspace only make calls faster: the chain's history of
 // omega (4 k_max n bytes; kept while that is at most a quarter of A's own,
 // k_max <= lda * element size / 16, or 16 MiB, so it never dominates what a
-// context needs) and the scratch of a subset's basis.  Neither may push a
-// problem out of the static workspace, which takes the same layout as a
-// context so that both run the same kernels.
+// context needs, and at most 4 GiB: a larger one belongs to an A of over
+// 16 GiB, whose passes take 2.5 ms and more against the 15 us it saves, and
+// which may need the card's memory itself) and the scratch of a subset's
+// basis.  Neither may push a problem out of the static workspace, which takes
+// the same layout as a context so that both run the same kernels.
 bool make_layout(const gcss_desc *d, int num_cu, Layout *L) {
   const int64_t hb = 4 * (int64_t)d->k_max * d->n;
-  const bool hist = hb <= std::max<int64_t>(d->n * d->lda * dtype_bytes(d->a_dtype) / 4, 16 << 20);
+  const int64_t quarter = d->n * d->lda * dtype_bytes(d->a_dtype) / 4;
+  const bool hist = hb <= std::max<int64_t>(std::min<int64_t>(quarter, (int64_t)4 << 30), 16 << 20);
   if (!make_layout_with(d, num_cu, hist, true, L)) return false;
   if (L->total > (size_t)GCSS_STATIC_SCRATCH_BYTES) {
     Layout S;
