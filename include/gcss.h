@@ -215,7 +215,7 @@ gcss_status gcss_reconstruction_error(gcss_ctx *h, const int64_t *idx, int32_t k
  * replaced or turned off (w = NULL).  gcss_select and gcss_select_async
  * write rows 0 .. n_selected-1 (binary32; FP8 columns include their
  * scale); other rows are left as they were.  Batched selection does not
- * write it.  Changing the pointer rebuilds gcss_select_async's graph.
+ * write it.  Changing the pointer or the stride rebuilds the captured loops.
  * Errors: GCSS_ERR_ARG (ldw < n, misaligned w).
  */
 gcss_status gcss_set_embedding(gcss_ctx *h, float *w, int64_t ldw);

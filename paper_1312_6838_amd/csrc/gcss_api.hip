@@ -968,9 +968,11 @@ gcss_status gcss_set_embedding(gcss_ctx *h, float *w, int64_t ldw) {
   if (check_ctx(h)) return GCSS_ERR_ARG;
   if (w && ldw < h->d.n) return fail(GCSS_ERR_ARG, "ldw (%lld) < n (%lld)", (long long)ldw, (long long)h->d.n);
   if (((uintptr_t)w) % 4) return fail(GCSS_ERR_ARG, "w must be 4-byte aligned");
-  if (w != h->emb) drop_graph(h);
+  if (!w) ldw = 0;
+  // the captured loops hold the pointer and the stride
+  if (w != h->emb || ldw != h->ldw) drop_graph(h);
   h->emb = w;
-  h->ldw = w ? ldw : 0;
+  h->ldw = ldw;
   return GCSS_OK;
 }
 
