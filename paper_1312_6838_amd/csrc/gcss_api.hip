@@ -924,8 +924,8 @@ gcss_status gcss_reconstruction_error(gcss_ctx *h, const int64_t *idx, int32_t k
                                  h->at<double>(h->L.f), h->at<double>(h->L.g), h->at<uint8_t>(h->L.mask),
                                  h->d.n, sb, k, h->d.k_max, h->F0(), kBasisTau, s));
       if (block) {
-        HIPCHK(launch_basis(bp, h->at<char>(h->L.scratch), h->A, pick, k, h->at<double>(h->L.Q), ldq, sb.st,
-                            h->basis_flag(), s));
+        HIPCHK(launch_basis(bp, h->at<char>(h->L.scratch), h->A, h->at<double>(h->L.g0), pick, k,
+                            h->at<double>(h->L.Q), ldq, sb.st, h->basis_flag(), s));
       } else {
         for (int i = 0; i < k; ++i) HIPCHK(enqueue_basis_step(h, sb));
         DevState hs;

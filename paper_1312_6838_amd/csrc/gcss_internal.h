@@ -254,9 +254,10 @@ struct BasisPlan {
 BasisPlan basis_plan(int64_t m, int64_t ldq, int kmax);
 // Q[:, 0..k) = an orthonormal basis of the columns pick[0..k) of A, in their
 // order, state t = k; *flag is 1 where it is not certified (the caller then
-// runs Gram-Schmidt), else 0
-hipError_t launch_basis(const BasisPlan &P, char *scr, const AView &A, const int64_t *pick, int k,
-                        double *Q, int64_t ldq, DevState *st, int *flag, hipStream_t s);
+// runs Gram-Schmidt), else 0; norm2: A's squared column norms
+hipError_t launch_basis(const BasisPlan &P, char *scr, const AView &A, const double *norm2,
+                        const int64_t *pick, int k, double *Q, int64_t ldq, DevState *st, int *flag,
+                        hipStream_t s);
 
 // ---- launchers (k_mfma.hip) ----
 // (scratch: parts of f where few columns share their rows' chunks)

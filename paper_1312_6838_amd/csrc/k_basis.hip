@@ -15,10 +15,14 @@
 //
 // Rounding leaves Y^T Y = I + E with E about eps cond(S)^2; the Newton step
 // takes the deviation to 3/8 E^2.  The result is used only where it is
-// certified: every pivot above kPivotRel of its column's squared norm, every
-// |E_ij| <= kDevMax (so ||E||^2 <= 2e-16 for 128 columns), Q^T Y as small.
+// certified: every pivot above kPivotRel of its column's squared norm in A,
+// every |E_ij| <= kDevMax (so ||E||^2 <= 2e-16 for 128 columns), Q^T Y as small.
 // Otherwise (dependent or nearly dependent columns) a flag is set, and the
-// caller runs Gram-Schmidt, whose rule for dropping columns decides.
+// caller runs Gram-Schmidt, whose rule for dropping columns decides.  (The
+// norm is that of the column as stored, as in that rule: what a chunk's S
+// still holds of a column that depends on earlier chunks is rounding, or an
+// exact remnant far below the rule's 1e-13, and against its own norm it would
+// always pass.)
 //
 // All products are FP64 on the matrix cores (v_mfma_f64_16x16x4: lane l gives
 // row l % 16 of the left and column l % 16 of the right operand at k = l / 16,
@@ -264,11 +268,13 @@ __device__ __forceinline__ double lane_value(double v, int x) {
 }
 
 __global__ __launch_bounds__(kCThreads) void k_bs_chol(const double *__restrict__ gram, int b,
+                                                       const int64_t *__restrict__ pick,
+                                                       const double *__restrict__ norm2,
                                                        double *__restrict__ T,
                                                        int *__restrict__ flag) {
   __shared__ double G[kBC * kCP];
   __shared__ double D[kBC * 16];  // inverses of the diagonal blocks, row-major 16 x 16 each
-  __shared__ double g0[kBC];
+  __shared__ double g0[kBC];  // the columns' squared norms in A
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   // the Gram matrix, identity past b (gram and T may be one buffer)
 #pragma unroll
@@ -277,8 +283,8 @@ __global__ __launch_bounds__(kCThreads) void k_bs_chol(const double *__restrict_
     double s = gram[e];
     if (i >= b || j >= b) s = i == j ? 1.0 : 0.0;
     G[i * kCP + j] = s;
-    if (i == j) g0[i] = s;
   }
+  if (threadIdx.x < kBC) g0[threadIdx.x] = (int)threadIdx.x < b ? norm2[pick[threadIdx.x]] : 1.0;
   __syncthreads();
   bool bad = false;
   for (int p = 0; p < kBC; p += 16) {
@@ -420,8 +426,9 @@ BasisPlan basis_plan(int64_t m, int64_t ldq, int kmax) {
   return P;
 }
 
-hipError_t launch_basis(const BasisPlan &P, char *scr, const AView &A, const int64_t *pick, int k,
-                        double *Q, int64_t ldq, DevState *st, int *flag, hipStream_t s) {
+hipError_t launch_basis(const BasisPlan &P, char *scr, const AView &A, const double *norm2,
+                        const int64_t *pick, int k, double *Q, int64_t ldq, DevState *st, int *flag,
+                        hipStream_t s) {
   const int64_t m = A.m;
   double *S = (double *)(scr + P.S), *Y = (double *)(scr + P.Y), *part = (double *)(scr + P.part),
          *W = (double *)(scr + P.W);
@@ -450,7 +457,8 @@ hipError_t launch_basis(const BasisPlan &P, char *scr, const AView &A, const int
     }
     tn(S, kBC, S);
     reduce(kBC, 0, b);
-    hipLaunchKernelGGL(k_bs_chol, dim3(1), dim3(kCThreads), 0, s, W, b, W, flag);
+    hipLaunchKernelGGL(k_bs_chol, dim3(1), dim3(kCThreads), 0, s, W, b, pick + t0, norm2, W,
+                       flag);
     nn(S, kBC, nullptr, Y, kBC, nullptr);
     if (t0 > 0) {
       tn(Q, t0, Y);
