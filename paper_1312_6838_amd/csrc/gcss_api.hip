@@ -107,8 +107,11 @@ bool make_layout_with(const gcss_desc *d, int num_cu, bool hist, bool basis, Lay
   L->mask0 = c.take<uint8_t>(n);
   L->mask = c.take<uint8_t>(n);
   L->part = c.take<ArgPart>(std::max(L->geo.grid, 1));
-  // (with the history, one row per step)
-  L->qpart = c.take<double>((size_t)std::max(L->geo.grid, 1) * (d->self_target ? k : 1));
+  // per-workgroup sums of the exact decrease: one row, reduced by the pass, or
+  // with the history one per step, reduced with the final objective
+  L->chain = chain_fits(m, r, (int)k, kChainLdsMax);
+  L->hist = L->chain && hist;
+  L->qpart = c.take<double>((size_t)std::max(L->geo.grid, 1) * (L->hist && d->self_target ? k : 1));
   L->npart = c.take<double>(1024);
   L->Q = c.take<double>((size_t)L->ldq * (k + 1));
   L->e1 = c.take<double>(L->ldq);
@@ -136,13 +139,11 @@ bool make_layout_with(const gcss_desc *d, int num_cu, bool hist, bool basis, Lay
   // the per-step chain: w history V (as Q), dot partials per row block of
   // 1024 rows (B = A: also C e2, m entries), and one norm and one q . w
   // partial per 32-row workgroup
-  L->chain = chain_fits(m, r, (int)k, kChainLdsMax);
   L->lp = (int64_t)up((size_t)(std::max<int64_t>(r, d->self_target ? m : 0) + k + 1), 4);
   L->V = c.take<double>((size_t)L->ldq * (k + 1));
   L->P = c.take<double>((size_t)chain_row_blocks(m) * L->lp);
   L->Pn = c.take<double>(chain_row_groups(m));
   L->Pu = c.take<double>(chain_row_groups(m));
-  L->hist = L->chain && hist;
   L->lp1 = (int64_t)up((size_t)k, 4);
   if (L->hist) {
     L->wh = c.take<float>((size_t)k * n);
