@@ -85,7 +85,10 @@ gcss_status gcss_workspace_size(const gcss_desc *d, size_t *bytes);
 /*
  * Create a context over the source matrix described by *d, on the current
  * HIP device.  workspace: device, >= gcss_workspace_size bytes, 256-byte
- * aligned, borrowed for the context's life.
+ * aligned, borrowed for the context's life.  (gcss_workspace_size includes
+ * parts that only make calls faster: a history of at most a quarter of A or
+ * 16 MiB, and scratch for gcss_reconstruction_error.  A smaller workspace that
+ * holds the context without them is accepted too.)
  * Errors: GCSS_ERR_ARG, GCSS_ERR_WORKSPACE, GCSS_ERR_DEVICE (no gfx950),
  * GCSS_ERR_UNSUPPORTED (m > 8192, the most rows the streaming kernel keeps
  * in registers).

@@ -82,12 +82,19 @@ class Selector:
             nbytes += batched_workspace_size(self.desc, *batched)
         if workspace is None:
             workspace = torch.empty(nbytes, dtype=torch.uint8, device=A.device)
-        elif (workspace.dtype != torch.uint8 or not workspace.is_cuda
-              or not workspace.is_contiguous() or workspace.numel() < nbytes):
-            raise ValueError(f"workspace must be a contiguous uint8 cuda tensor of >= {nbytes} bytes")
+        bad = ValueError(f"workspace must be a contiguous uint8 cuda tensor of >= {nbytes} bytes")
+        if (workspace.dtype != torch.uint8 or not workspace.is_cuda or not workspace.is_contiguous()
+                or (batched is not None and workspace.numel() < nbytes)):
+            raise bad
         self.ws = workspace
-        self.ws_bytes = nbytes
-        self.h = create(self.desc, self.ws.data_ptr(), nbytes)
+        self.ws_bytes = min(nbytes, workspace.numel())
+        try:
+            # (create may take a smaller one without the parts that only speed calls up)
+            self.h = create(self.desc, self.ws.data_ptr(), self.ws_bytes)
+        except GcssError as e:
+            if e.status == ERR_WORKSPACE and self.ws_bytes < nbytes:
+                raise bad from e
+            raise
         self.B = None
         self.r = 0
 

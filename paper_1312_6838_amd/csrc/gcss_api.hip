@@ -179,16 +179,23 @@ bool make_layout_with(const gcss_desc *d, int num_cu, bool hist, bool basis, Lay
 // 16 GiB, whose passes take 2.5 ms and more against the 15 us it saves, and
 // which may need the card's memory itself) and the scratch of a subset's
 // basis.  Neither may push a problem out of the static workspace, which takes
-// the same layout as a context so that both run the same kernels.
-bool make_layout(const gcss_desc *d, int num_cu, Layout *L) {
+// the same layout as a context so that both run the same kernels.  The choice
+// follows from the description alone (not from the device's CU count, which
+// gcss_workspace_size does not know), except that a workspace of under the
+// full layout's size (`avail`) that holds the rest is taken without them: what
+// is asked for does not grow steadily with n and k_max, and a caller may keep
+// one workspace, sized for the largest problem, for several.
+bool make_layout(const gcss_desc *d, int num_cu, Layout *L, size_t avail = SIZE_MAX) {
   const int64_t hb = 4 * (int64_t)d->k_max * d->n;
   const int64_t quarter = d->n * d->lda * dtype_bytes(d->a_dtype) / 4;
   const bool hist = hb <= std::max<int64_t>(std::min<int64_t>(quarter, (int64_t)4 << 30), 16 << 20);
-  if (!make_layout_with(d, num_cu, hist, true, L)) return false;
-  if (L->total > (size_t)GCSS_STATIC_SCRATCH_BYTES) {
-    Layout S;
-    if (make_layout_with(d, num_cu, false, false, &S) && S.total <= (size_t)GCSS_STATIC_SCRATCH_BYTES) *L = S;
-  }
+  Layout plain;
+  if (!make_layout_with(d, kPlanCU, hist, true, L) || !make_layout_with(d, kPlanCU, false, false, &plain))
+    return false;
+  const size_t cap = (size_t)GCSS_STATIC_SCRATCH_BYTES;
+  const bool parts = L->total <= cap || plain.total > cap;
+  if (!make_layout_with(d, num_cu, parts && hist, parts, L)) return false;
+  if (L->total > avail && make_layout_with(d, num_cu, false, false, &plain)) *L = plain;
   return true;
 }
 
@@ -601,7 +608,7 @@ gcss_status init_ctx(gcss_ctx *h, const gcss_desc *d, void *workspace, size_t ws
     return fail(GCSS_ERR_DEVICE, "device %d is %s, not gfx950", dev, prop.gcnArchName);
   const int num_cu = std::min(prop.multiProcessorCount, kPlanCU);
   Layout L;
-  if (!make_layout(d, num_cu, &L)) return fail(GCSS_ERR_UNSUPPORTED, "m too large for the stream kernel");
+  if (!make_layout(d, num_cu, &L, ws_bytes)) return fail(GCSS_ERR_UNSUPPORTED, "m too large for the stream kernel");
   if (!workspace) return fail(GCSS_ERR_WORKSPACE, "null workspace");
   if (((uintptr_t)workspace) % 256) return fail(GCSS_ERR_WORKSPACE, "workspace must be 256-byte aligned");
   if (ws_bytes < L.total)
