@@ -42,6 +42,16 @@ gcss_status fail(gcss_status s, const char *fmt, ...) {
 constexpr int kPlanCU = 256;       // CU count used to size the workspace (MI355X)
 constexpr int kSpareSlots = GCSS_ASYNC_SPARE_STEPS;  // extra steps of a captured loop (rejected picks)
 constexpr double kBasisTau = 1e-13;  // dependence threshold of the basis-only mode
+constexpr double kTauDefault = 1e-4;
+// Smallest tau whose selections use the chain's history of omega.  Its binary32
+// coefficients (for an explicit target, of binary32 dots) leave up to d = 2e-6 of
+// a column in Q's span after the first projection (500 picks, each off by up to
+// 1e-7), against 1e-16 from FP64 dots; an accepted pick keeps sqrt(tau) of it,
+// so the second projection's rounding, and what a basis that is not quite
+// orthonormal lets pass, grow by d / sqrt(tau): 0.2% here, 0.02% at the default.
+// Picks of 1e-12 of their columns (tau = 1e-28) came out parallel to earlier
+// ones.  Below, c1 comes from FP64 dots, as without a history.
+constexpr double kHistTau = 1e-6;
 constexpr size_t kChainLdsMax = 44 * 1024;  // dynamic LDS the chain's row kernels may take
 
 inline size_t up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -173,12 +183,12 @@ bool make_layout_with(const gcss_desc *d, int num_cu, bool hist, bool basis, Lay
 }
 
 // Two parts of the workspace only make calls faster: the chain's history of
-// omega (4 k_max n bytes; kept while that is at most a quarter of A's own,
-// k_max <= lda * element size / 16, or 16 MiB, so it never dominates what a
-// context needs, and at most 4 GiB: a larger one belongs to an A of over
-// 16 GiB, whose passes take 2.5 ms and more against the 15 us it saves, and
-// which may need the card's memory itself) and the scratch of a subset's
-// basis.  Neither may push a problem out of the static workspace, which takes
+// omega (4 k_max n bytes; kept for tau >= kHistTau while that is at most a
+// quarter of A's own, k_max <= lda * element size / 16, or 16 MiB, so it never
+// dominates what a context needs, and at most 4 GiB: a larger one belongs to an
+// A of over 16 GiB, whose passes take 2.5 ms and more against the 15 us it
+// saves, and which may need the card's memory itself) and the scratch of a
+// subset's basis.  Neither may push a problem out of the static workspace, which takes
 // the same layout as a context so that both run the same kernels.  The choice
 // follows from the description alone (not from the device's CU count, which
 // gcss_workspace_size does not know), except that a workspace of under the
@@ -188,7 +198,9 @@ bool make_layout_with(const gcss_desc *d, int num_cu, bool hist, bool basis, Lay
 bool make_layout(const gcss_desc *d, int num_cu, Layout *L, size_t avail = SIZE_MAX) {
   const int64_t hb = 4 * (int64_t)d->k_max * d->n;
   const int64_t quarter = d->n * d->lda * dtype_bytes(d->a_dtype) / 4;
-  const bool hist = hb <= std::max<int64_t>(std::min<int64_t>(quarter, (int64_t)4 << 30), 16 << 20);
+  const double tau = d->tau > 0.0 ? d->tau : kTauDefault;
+  const bool hist = tau >= kHistTau &&
+                    hb <= std::max<int64_t>(std::min<int64_t>(quarter, (int64_t)4 << 30), 16 << 20);
   Layout plain;
   if (!make_layout_with(d, kPlanCU, hist, true, L) || !make_layout_with(d, kPlanCU, false, false, &plain))
     return false;
@@ -633,7 +645,7 @@ gcss_status init_ctx(gcss_ctx *h, const gcss_desc *d, void *workspace, size_t ws
   h->num_cu = num_cu;
   h->stream = (hipStream_t)d->stream;
   h->d = *d;
-  if (!(h->d.tau > 0.0)) h->d.tau = 1e-4;
+  if (!(h->d.tau > 0.0)) h->d.tau = kTauDefault;
   h->L = L;
   h->tune = tune;
   // per-step work: the six-kernel chain where it fits, else the general

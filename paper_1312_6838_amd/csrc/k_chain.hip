@@ -35,7 +35,11 @@
 //
 // c1 is off by binary32 rounding (1e-7 ||a||); the second projection, formed
 // in FP64 from e1 as it is, takes that out with the rest of Q's span, so e2 is
-// orthogonal to Q to FP64 rounding of ||e1|| as before.  The partials of a
+// orthogonal to Q to FP64 rounding of ||e1||.  That is as good as two projections
+// in FP64 while an accepted pick's ||e2|| is far above 1e-7 ||a||, so the
+// history is kept for tau >= 1e-6 only (kHistTau in gcss_api.hip).  Over 80
+// random problems (m 100 .. 8192, k 10 .. 200, tau 1e-4 .. 1e-6) the largest
+// |Q^T Q - I| of the two agree to 3% in the mean, 4e-16 .. 1.2e-14 both.  The partials of a
 // consumer grow with m (m / 32 rows of r + t), so this form serves shapes
 // whose partials stay small; above, S1 without partials replaces K1 and K2.
 // The chain's kernel time per step on MI355X, six kernels -> now: m = 1024,
