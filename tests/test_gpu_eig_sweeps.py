@@ -1,0 +1,34 @@
+"""The block Jacobi's limit on sweeps: spectra that fall by seven to ten decades
+(the entries of their small eigenvalues' block are within a few rounding errors
+of the sweeps' zero) take 20 to 45 sweeps at these sizes, and none of them may
+be given up.  Against the eigenvalues from numpy."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("l", [333, 500])
+def test_steep_spectra_converge(gpu, l):
+    m, n = l + 50, 2 * l
+    rng = np.random.default_rng(l)
+    A = np.zeros((n, (m + 63) // 64 * 64), np.float32)
+    A[:, :m] = rng.standard_normal((n, m))
+    s = gpu.Selector(torch.from_numpy(A).cuda(), m, k_max=l, self_target=True)
+    s.set_target(None)
+    W = torch.zeros(l, n, dtype=torch.float32, device="cuda")
+    s.set_embedding(W)
+    assert s.select(l)[2] == l
+    V = np.linalg.qr(rng.standard_normal((n, l)))[0].T
+    for decades in (7.0, 7.5, 8.0, 10.0):
+        U = np.linalg.qr(rng.standard_normal((l, l)))[0]
+        X = (U * 10.0 ** (-decades * np.arange(l) / l)) @ V
+        W.copy_(torch.from_numpy(X))
+        Wd = W.cpu().numpy().astype(np.float64)
+        want = np.linalg.eigvalsh(Wd @ Wd.T)[::-1]
+        _, sigma, _, _ = s.rank_k(l, l, want_u=False, want_v=False)
+        # Jacobi in FP64: every sweep's l rotations per entry round by eps of the largest
+        # eigenvalue, so eps l sweeps, here taken as eps l^2
+        assert np.max(np.abs(np.asarray(sigma) ** 2 - np.maximum(want, 0.0))) <= 2.3e-16 * l * l * want[0]
+    s.close()
