@@ -212,13 +212,26 @@ __global__ __launch_bounds__(256) void k_jac_floor(const double *__restrict__ G,
 // triangle, whose 528 blocks of 2 x 2 are one per thread of nine waves; the
 // other waves apply the round's rotations to part of V meanwhile, and all but
 // wave 0 to the rest while that forms the next rotations from S.  V is kept by
-// columns, so that a wave's 64 rows are consecutive words.  The rotation's
-// tangent is taken in binary32 (V only has to be orthogonal, so c and s are
-// normalised in FP64; a tangent off by 1e-7 leaves 1e-7 of the entry, which
-// later rotations see).  An inner round took 1.7 us with 256 threads, the
-// indices in LDS, FP64 roots and divisions and V updated before the next
-// rotations; now 1.1 us (a solve of round 0: 107 -> 73 us, of another: 41 us).
+// columns, so that a wave's 64 rows are consecutive words.  The rotations'
+// quotients and roots are FP64 Newton steps on the hardware's estimates (the
+// compiler's correctly rounded ones are several times as long; a tangent in
+// binary32 measured no faster).  An inner round took 1.7 us with 256 threads,
+// the indices in LDS, correctly rounded FP64 roots and divisions and V updated
+// before the next rotations; now 1.1 us (a solve of round 0: 107 -> 73 us, of
+// another: 41 us).
 constexpr int kJacThreads = 1024;
+
+// 1 / x and x^-1/2: two Newton steps on the hardware's estimate
+__device__ __forceinline__ double jac_rcp(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(r, fma(-x, r, 1.0), r);
+  return fma(r, fma(-x, r, 1.0), r);
+}
+__device__ __forceinline__ double jac_rsq(double x) {
+  double r = __builtin_amdgcn_rsq(x);
+  r = fma(0.5 * r, fma(-r * x, r, 1.0), r);
+  return fma(0.5 * r, fma(-r * x, r, 1.0), r);
+}
 
 __device__ __forceinline__ void jac_inner_pair(bool full, int rr, int p, int &x, int &y) {
   if (full) {
@@ -312,15 +325,11 @@ __global__ __launch_bounds__(kJacThreads) void k_jac_solve(const double *__restr
       rot = !negligible(gxy, gxx, gyy, fl);
       if (rot) {
         // the smaller root of t^2 + 2 tau t = 1, tau = (gyy - gxx) / (2 gxy);
-        // |tau| < 1e15 (gxy is above kJacAbs max g)
-        const float tau = (float)((gyy - gxx) * __builtin_amdgcn_rcp(2.0 * gxy));
-        const float tf = copysignf(
-            __builtin_amdgcn_rcpf(fabsf(tau) + __builtin_amdgcn_sqrtf(fmaf(tau, tau, 1.f))), tau);
-        const double t = (double)tf, h = fma(t, t, 1.0);
-        // c = h^-1/2: two Newton steps on the hardware's estimate
-        c = __builtin_amdgcn_rsq(h);
-        c = fma(0.5 * c, fma(-h * c, c, 1.0), c);
-        c = fma(0.5 * c, fma(-h * c, c, 1.0), c);
+        // |tau| < 1e19 (gxy is above kJacAbs times the largest initial g_xx, and
+        // no g_xx passes the trace, at most kRankMaxL of those)
+        const double tau = (gyy - gxx) * jac_rcp(2.0 * gxy), w = fma(tau, tau, 1.0);
+        const double t = copysign(jac_rcp(fma(w, jac_rsq(w), fabs(tau))), tau);
+        c = jac_rsq(fma(t, t, 1.0));
         sv = t * c;
       }
       cs[rr & 1][lane] = make_double2(c, sv);
@@ -348,7 +357,8 @@ __global__ __launch_bounds__(kJacThreads) void k_jac_solve(const double *__restr
     const bool any = nrot[rr & 1] != 0;
     if (any && sact) {
       // S <- J^T S J by 2 x 2 blocks (row pair P, column pair Q), in the lower
-      // triangle; the diagonal blocks' two equal entries are one
+      // triangle; the diagonal blocks' two equal entries are one (zero once
+      // rotated)
       const double2 cp = J[P], cq = J[Q];
       double *const e00 = jac_low(S, x0.v, x1.v), *const e01 = jac_low(S, x0.v, y1.v);
       double *const e10 = jac_low(S, y0.v, x1.v), *const e11 = jac_low(S, y0.v, y1.v);
@@ -356,7 +366,7 @@ __global__ __launch_bounds__(kJacThreads) void k_jac_solve(const double *__restr
       const double r00 = cp.x * a00 - cp.y * a10, r01 = cp.x * a01 - cp.y * a11;
       const double r10 = cp.y * a00 + cp.x * a10, r11 = cp.y * a01 + cp.x * a11;
       *e00 = cq.x * r00 - cq.y * r01;
-      *e01 = cq.y * r00 + cq.x * r01;
+      *e01 = P == Q && cp.y != 0.0 ? 0.0 : cq.y * r00 + cq.x * r01;
       if (P != Q) *e10 = cq.x * r10 - cq.y * r11;
       *e11 = cq.y * r10 + cq.x * r11;
     } else if (any && wave >= kJacSWaves) {
