@@ -110,10 +110,11 @@ __device__ __forceinline__ uint32_t fp8x4_rne_sat(const float (&q)[4], const f32
   return c | (((lo & 0xFFFFu) | (hi << 16)) & 0x80808080u);
 }
 
-constexpr int kQuantV = 8;  // 16-byte loads per thread that hold a column's part
+constexpr int kQuantV = 8;  // most 16-byte loads per thread that hold a column's part
 
-// FP8: WPC waves of a 256-thread workgroup per column (ldo <= 2048 WPC).
-template <int WPC>
+// FP8: WPC waves of a 256-thread workgroup per column, V loads per thread
+// (ldo <= 256 WPC V).
+template <int WPC, int V>
 __global__ __launch_bounds__(256) void k_quant_fp8(const float *__restrict__ a, int64_t m,
                                                    int64_t n, int64_t lda,
                                                    uint8_t *__restrict__ out, int64_t ldo,
@@ -124,17 +125,17 @@ __global__ __launch_bounds__(256) void k_quant_fp8(const float *__restrict__ a, 
   const int tid = threadIdx.x % (64 * WPC);
   const bool live = col < n;  // (false only for whole waves, WPC = 1)
   const float *src = a + (live ? col : n - 1) * lda;
-  f32x4_t v[kQuantV];
+  f32x4_t v[V];
   float amax = 0.f;
 #pragma unroll
-  for (int u = 0; u < kQuantV; ++u) {
+  for (int u = 0; u < V; ++u) {
     const int64_t j = 4 * (int64_t)(tid + 64 * WPC * u);
     // (a chunk past m reads the column's first one; a chunk that straddles
     // m ends inside lda, a multiple of four)
     v[u] = __builtin_nontemporal_load((const f32x4_t *)(src + (j < m ? j : 0)));
   }
 #pragma unroll
-  for (int u = 0; u < kQuantV; ++u) {
+  for (int u = 0; u < V; ++u) {
     const int64_t j = 4 * (int64_t)(tid + 64 * WPC * u);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -155,7 +156,7 @@ __global__ __launch_bounds__(256) void k_quant_fp8(const float *__restrict__ a, 
   const bool fast = s >= 0x1p-60f && s <= 0x1p60f;
   const float r = 1.f / s;
 #pragma unroll
-  for (int u = 0; u < kQuantV; ++u) {
+  for (int u = 0; u < V; ++u) {
     const int64_t c = tid + 64 * WPC * u;
     if (4 * c < ldo) {
       uint32_t code = 0;
@@ -203,7 +204,10 @@ __global__ __launch_bounds__(256) void k_quant_bf16(const float *__restrict__ a,
 // The wide kernels need 16-byte aligned columns of A and whole packed words
 // per output column; FP8 also a column that its waves' registers hold.  One
 // wave per column keeps the maximum inside the wave, as far as its registers
-// go (2048 rows); above that four waves share a column.  Measured on MI355X,
+// go (2048 rows); above that four waves share a column.  A wave issues its V
+// loads whatever the column's length, so V is the smallest that holds it (with
+// eight for all, columns of up to 128 rows were slower than element by element:
+// m = 50, n = 120000 44 -> 56 us, with one 33 us).  Measured on MI355X,
 // element-wise kernel -> these: FP8 8192 x 32768 693 -> 227 us (5.9 TB/s),
 // FP8 1024 x 262144 615 -> 218 us, FP8 333 x 100003 78 -> 52 us; BF16 8192 x
 // 32768 416 -> 259 us (6.2 TB/s).  Other shapes take the element-wise kernel.
@@ -217,12 +221,15 @@ hipError_t launch_quantize(const float *a, int64_t m, int64_t n, int64_t lda, in
                        dim3(256), 0, s, a, m, lda, (uint16_t *)out, ldo, cpc, total);
   } else if (dtype == DT_FP8 && wide && ldo % 4 == 0 && (uintptr_t)out % 4 == 0 &&
              ldo <= 4 * kQuantV * 256) {
-    if (ldo <= 4 * kQuantV * 64)
-      hipLaunchKernelGGL(k_quant_fp8<1>, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, a, m, n,
+    auto run = [&](auto fn, int wpc) {
+      hipLaunchKernelGGL(fn, dim3((unsigned)((n + 4 / wpc - 1) / (4 / wpc))), dim3(256), 0, s, a, m, n,
                          lda, (uint8_t *)out, ldo, scales);
-    else
-      hipLaunchKernelGGL(k_quant_fp8<4>, dim3((unsigned)n), dim3(256), 0, s, a, m, n, lda,
-                         (uint8_t *)out, ldo, scales);
+    };
+    if (ldo <= 256) run(k_quant_fp8<1, 1>, 1);
+    else if (ldo <= 512) run(k_quant_fp8<1, 2>, 1);
+    else if (ldo <= 1024) run(k_quant_fp8<1, 4>, 1);
+    else if (ldo <= 2048) run(k_quant_fp8<1, kQuantV>, 1);
+    else run(k_quant_fp8<4, kQuantV>, 4);
   } else {
     hipLaunchKernelGGL(k_quantize, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, a, m, n, lda,
                        dtype, out, ldo, scales);

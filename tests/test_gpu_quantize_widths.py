@@ -1,0 +1,26 @@
+"""FP8 quantizer: both sides of the column lengths at which a wave's number of
+loads changes, byte for byte against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from tests.test_gpu_quantize import _inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("m,lda,ldo", [
+    (3, 4, 256), (255, 256, 256), (253, 256, 260), (256, 256, 512), (509, 512, 512), (510, 512, 516),
+    (512, 512, 1024), (1023, 1024, 1024), (1024, 1024, 1028), (1027, 1028, 2048)])
+def test_loads_per_wave(gpu, m, lda, ldo):
+    n = 11
+    A = _inputs(m, n, lda, m + ldo)
+    dA = torch.from_numpy(A).cuda()
+    out = torch.full((n, ldo), 0xAB, dtype=torch.uint8, device="cuda")
+    sc = torch.full((n,), -1.0, device="cuda")
+    gpu.quantize(dA.data_ptr(), m, n, lda, gpu.FP8_E4M3, out.data_ptr(), ldo, sc.data_ptr())
+    codes, scl = oracle.quantize_fp8(np.ascontiguousarray(A[:, :m]), m, ldo=ldo)
+    ok = scl > 0  # (a column whose scale underflows to zero has no defined codes)
+    assert np.array_equal(sc.cpu().numpy().view(np.int32), scl.astype(np.float32).view(np.int32))
+    assert np.array_equal(out.cpu().numpy()[ok], codes[ok])
