@@ -82,7 +82,7 @@ hipError_t launch_bf16_to_f32(const void *in, int64_t m, int64_t n, int64_t ldi,
 // Bound by memory: m n * (4 + output bytes), plus the pads of the output.
 // The element-wise kernel above read FP8 columns twice with 4-byte loads,
 // stored single bytes and spent ~30 vector instructions per element on a
-// full division and the integer encoder: 733 us for 8192 x 32768 (1.8 TB/s).
+// full division and the integer encoder: 697 us for 8192 x 32768 (1.9 TB/s).
 // Here a column's values stay in registers between its maximum and its
 // codes, and the quotient by the column's scale s is formed from r = 1 / s:
 // q0 = x r, q = q0 + r (x - q0 s) with the residual exact by FMA, which is
@@ -180,15 +180,24 @@ __global__ __launch_bounds__(256) void k_quant_fp8(const float *__restrict__ a, 
 }
 
 // BF16: eight elements per thread, one 16-byte store; cpc = ldo / 8.
+// NT: loads and stores bypass the caches.
+template <bool NT>
 __global__ __launch_bounds__(256) void k_quant_bf16(const float *__restrict__ a, int64_t m,
                                                     int64_t lda, uint16_t *__restrict__ out,
                                                     int64_t ldo, int64_t cpc, int64_t total) {
   typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+  auto load = [](const float *p) -> f32x4_t {
+    if constexpr (NT) return __builtin_nontemporal_load((const f32x4_t *)p);
+    else return *(const f32x4_t *)p;
+  };
   for (int64_t x = (int64_t)blockIdx.x * 256 + threadIdx.x; x < total; x += (int64_t)gridDim.x * 256) {
-    const int64_t col = x / cpc, j = 8 * (x - col * cpc);
+    // (a division in 64 bits takes several times the conversion's instructions)
+    const int64_t col = total <= UINT32_MAX ? (int64_t)((uint32_t)x / (uint32_t)cpc) : x / cpc;
+    const int64_t j = 8 * (x - col * cpc);
     const float *src = a + col * lda;
-    const f32x4_t lo = __builtin_nontemporal_load((const f32x4_t *)(src + (j < m ? j : 0)));
-    const f32x4_t hi = __builtin_nontemporal_load((const f32x4_t *)(src + (j + 4 < m ? j + 4 : 0)));
+    f32x4_t lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;  // (pads are not loaded)
+    if (j < m) lo = load(src + j);
+    if (j + 4 < m) hi = load(src + j + 4);
     u32x4_t o;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
@@ -197,29 +206,39 @@ __global__ __launch_bounds__(256) void k_quant_bf16(const float *__restrict__ a,
       const uint32_t b0 = j + e < m ? bf16_rne(x0) : 0u, b1 = j + e + 1 < m ? bf16_rne(x1) : 0u;
       o[w] = b0 | (b1 << 16);
     }
-    __builtin_nontemporal_store(o, (u32x4_t *)(out + col * ldo + j));
+    u32x4_t *const dst = (u32x4_t *)(out + col * ldo + j);
+    if constexpr (NT) __builtin_nontemporal_store(o, dst);
+    else *dst = o;
   }
 }
 
 // The wide kernels need 16-byte aligned columns of A and whole packed words
-// per output column; FP8 also a column that its waves' registers hold.  One
+// per output column; FP8 also a column that its waves' registers hold, and one
+// of more than 64 codes (up to there an element per lane is 2% faster).  One
 // wave per column keeps the maximum inside the wave, as far as its registers
 // go (2048 rows); above that four waves share a column.  A wave issues its V
 // loads whatever the column's length, so V is the smallest that holds it (with
 // eight for all, columns of up to 128 rows were slower than element by element:
-// m = 50, n = 120000 44 -> 56 us, with one 33 us).  Measured on MI355X,
-// element-wise kernel -> these: FP8 8192 x 32768 693 -> 227 us (5.9 TB/s),
-// FP8 1024 x 262144 615 -> 218 us, FP8 333 x 100003 78 -> 52 us; BF16 8192 x
-// 32768 416 -> 259 us (6.2 TB/s).  Other shapes take the element-wise kernel.
+// m = 50, n = 120000 44 -> 56 us, with one 33 us).  The BF16 kernel bypasses the
+// caches only where A and the output together exceed the last-level one (256
+// MB): below it 2048 x 20000 takes 37 us against 42 so, and 64 x 200000 with 192
+// rows of pads 30 against 35 (element by element 31); above it 8192 x 20000 159
+// against 167 us.  (FP8 gains and loses a tenth either way.)
+// Measured on MI355X, element-wise kernel -> these: FP8 8192 x 32768 697 ->
+// 225 us (5.97 TB/s), FP8 1024 x 262144 614 -> 223 us, FP8 333 x 100003 77 ->
+// 43 us; BF16 8192 x 32768 408 -> 261 us (6.2 TB/s), BF16 333 x 100003 42 ->
+// 35 us.  Other shapes take the element-wise kernel.
 hipError_t launch_quantize(const float *a, int64_t m, int64_t n, int64_t lda, int dtype,
                            void *out, int64_t ldo, float *scales, hipStream_t s) {
   const bool wide = lda % 4 == 0 && (uintptr_t)a % 16 == 0;
   if (dtype == DT_BF16 && wide && ldo % 8 == 0 && (uintptr_t)out % 16 == 0) {
     const int64_t cpc = ldo / 8, total = n * cpc;
     const int64_t blocks = (total + 255) / 256;
-    hipLaunchKernelGGL(k_quant_bf16, dim3((unsigned)(blocks < (1 << 20) ? blocks : (1 << 20))),
-                       dim3(256), 0, s, a, m, lda, (uint16_t *)out, ldo, cpc, total);
-  } else if (dtype == DT_FP8 && wide && ldo % 4 == 0 && (uintptr_t)out % 4 == 0 &&
+    const bool nt = n * (4 * m + 2 * ldo) > (int64_t)256 << 20;
+    hipLaunchKernelGGL(nt ? k_quant_bf16<true> : k_quant_bf16<false>,
+                       dim3((unsigned)(blocks < (1 << 20) ? blocks : (1 << 20))), dim3(256), 0, s, a, m,
+                       lda, (uint16_t *)out, ldo, cpc, total);
+  } else if (dtype == DT_FP8 && wide && ldo % 4 == 0 && (uintptr_t)out % 4 == 0 && ldo > 64 &&
              ldo <= 4 * kQuantV * 256) {
     auto run = [&](auto fn, int wpc) {
       hipLaunchKernelGGL(fn, dim3((unsigned)((n + 4 / wpc - 1) / (4 / wpc))), dim3(256), 0, s, a, m, n,
