@@ -213,8 +213,7 @@ __global__ __launch_bounds__(256) void k_quant_bf16(const float *__restrict__ a,
 }
 
 // The wide kernels need 16-byte aligned columns of A and whole packed words
-// per output column; FP8 also a column that its waves' registers hold, and one
-// of more than 64 codes (up to there an element per lane is 2% faster).  One
+// per output column; FP8 also a column that its waves' registers hold.  One
 // wave per column keeps the maximum inside the wave, as far as its registers
 // go (2048 rows); above that four waves share a column.  A wave issues its V
 // loads whatever the column's length, so V is the smallest that holds it (with
@@ -238,7 +237,7 @@ hipError_t launch_quantize(const float *a, int64_t m, int64_t n, int64_t lda, in
     hipLaunchKernelGGL(nt ? k_quant_bf16<true> : k_quant_bf16<false>,
                        dim3((unsigned)(blocks < (1 << 20) ? blocks : (1 << 20))), dim3(256), 0, s, a, m,
                        lda, (uint16_t *)out, ldo, cpc, total);
-  } else if (dtype == DT_FP8 && wide && ldo % 4 == 0 && (uintptr_t)out % 4 == 0 && ldo > 64 &&
+  } else if (dtype == DT_FP8 && wide && ldo % 4 == 0 && (uintptr_t)out % 4 == 0 &&
              ldo <= 4 * kQuantV * 256) {
     auto run = [&](auto fn, int wpc) {
       hipLaunchKernelGGL(fn, dim3((unsigned)((n + 4 / wpc - 1) / (4 / wpc))), dim3(256), 0, s, a, m, n,
