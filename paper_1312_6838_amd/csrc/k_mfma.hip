@@ -197,10 +197,12 @@ __device__ __forceinline__ float4 load4(const void *base, int64_t off) {
 // at r0; one half on it) and the sum is doubled.
 //
 // Few columns leave most of the chip idle (one workgroup per NT of them), so
-// then the row chunks are shared by gridDim.y workgroups: y takes the chunks
-// y, y + gridDim.y, ... and writes its part of f to fp[y * n + j] (y = 0 also
-// g), which k_init_finish adds in order.
-template <int DT, int RB, int NB, int BKT, bool TRI, bool DB>
+// then the row chunks are shared (SHARE) by gridDim.y workgroups: y takes the
+// chunks y, y + gridDim.y, ... and writes its part of f to fp[y * n + j] (y = 0
+// also g), which k_init_finish adds in order.  (An instance of its own: with
+// the chunks' stride in a register the unshared one took up to 1% longer,
+// 263.0 -> 265.0 us at m = 2000, n = 9000, r = 150.)
+template <int DT, int RB, int NB, int BKT, bool TRI, bool DB, bool SHARE>
 __global__ __launch_bounds__(256) void k_init(const float *__restrict__ X, int64_t ldx,
                                               int64_t R, AView A, double *__restrict__ f0,
                                               double *__restrict__ g0,
@@ -235,7 +237,7 @@ __global__ __launch_bounds__(256) void k_init(const float *__restrict__ X, int64
 
   const int64_t nchunks = (R + RT - 1) / RT;
   const int64_t ksteps = (m + BKT - 1) / BKT;
-  for (int64_t rc = blockIdx.y; rc < nchunks; rc += gridDim.y) {
+  for (int64_t rc = SHARE ? blockIdx.y : 0; rc < nchunks; rc += SHARE ? gridDim.y : 1) {
     const int64_t r0 = rc * RT;
     f32x4 acc[RB][NB];
 #pragma unroll
@@ -397,7 +399,7 @@ __global__ __launch_bounds__(256) void k_init(const float *__restrict__ X, int64
     if (j < n) {
       const double fv = ((red[0][tid] + red[1][tid]) + red[2][tid]) + red[3][tid];
       const double sc = col_scale(A, j);
-      if (gridDim.y > 1) {
+      if constexpr (SHARE) {
         fp[(int64_t)blockIdx.y * n + j] = fv;
         if (blockIdx.y == 0) g0[j] = sc * sc * gs[tid];
         return;
@@ -2122,17 +2124,21 @@ static hipError_t init_t(const float *X, int64_t ldx, int64_t R, const AView &A,
   constexpr bool kFitsDB = 2 * (64 * RB + 16 * NB) * (BKT + 4) * 4 + 8 * 1024 <= 160 * 1024;
   const unsigned grid = (unsigned)((A.n + 16 * NB - 1) / (16 * NB));
   const int ny = init_share(grid, (R + 64 * RB - 1) / (64 * RB), A.n, sc);
-  bool done = false;
-  if constexpr (kFitsDB) {
-    if (mfma_db()) {
-      hipLaunchKernelGGL((k_init<DT, RB, NB, BKT, TRI, true>), dim3(grid, ny), dim3(256), 0, s, X,
+  auto run = [&](auto db) {
+    constexpr bool DB = decltype(db)::value;
+    if (ny > 1)
+      hipLaunchKernelGGL((k_init<DT, RB, NB, BKT, TRI, DB, true>), dim3(grid, ny), dim3(256), 0, s, X,
                          ldx, R, A, f0, g0, mask0, sc.fp);
-      done = true;
-    }
+    else
+      hipLaunchKernelGGL((k_init<DT, RB, NB, BKT, TRI, DB, false>), dim3(grid), dim3(256), 0, s, X, ldx,
+                         R, A, f0, g0, mask0, (double *)nullptr);
+  };
+  if constexpr (kFitsDB) {
+    if (mfma_db()) run(std::true_type{});
+    else run(std::false_type{});
+  } else {
+    run(std::false_type{});
   }
-  if (!done)
-    hipLaunchKernelGGL((k_init<DT, RB, NB, BKT, TRI, false>), dim3(grid, ny), dim3(256), 0, s, X,
-                       ldx, R, A, f0, g0, mask0, sc.fp);
   return init_finish<TRI>(A, sc, ny, f0, g0, mask0, s);
 }
 
