@@ -1003,13 +1003,14 @@ gcss_status gcss_set_embedding(gcss_ctx *h, float *w, int64_t ldw) {
 constexpr int kMaxSweeps = 60;
 constexpr int kEigCheck = 4;  // subspace iterations between Rayleigh-Ritz checks
 
-// Block Jacobi sweeps on the prepared G until it is diagonal.
-static gcss_status run_jacobi(gcss_ctx *h, const RankPlan &P, char *scr) {
+// Block Jacobi sweeps on the prepared G of l indices until it is diagonal.
+static gcss_status run_jacobi(gcss_ctx *h, const RankPlan &P, char *scr, int l) {
+  if (l < 2) return GCSS_OK;  // (its padding is diagonal)
   hipStream_t s = h->stream;
   int conv = 1;
   std::vector<int> flags((size_t)(P.L / 64));
   // several sweeps between two looks at the flags (a look costs a copy and a
-  // wait, about 20 us; a sweep after the last one needed returns at once)
+  // wait, about 20 us; a sweep after the last one needed only its launches)
   constexpr int kLook = 3;
   for (int sweep = 0; sweep < kMaxSweeps && conv;) {
     for (int x = 0; x < kLook; ++x, ++sweep) HIPCHK(launch_jacobi_sweep(P, scr, sweep == 0, s));
@@ -1071,7 +1072,7 @@ gcss_status gcss_top_eig(gcss_ctx *h, int32_t s_block, int32_t max_iters, double
     // whose eigenvalues approximate C's leading ones
     if (!check) continue;
     HIPCHK(launch_wgram2(E.P, Qf, Y, ldq, sb, m, rs, st));
-    gcss_status g = run_jacobi(h, E.P, rs);
+    gcss_status g = run_jacobi(h, E.P, rs, sb);
     if (g) return g;
     HIPCHK(launch_eig_order(E.P, rs, sb, k, st));
     HIPCHK(hipMemcpyAsync(sig.data(), rs + E.P.sigma, sizeof(double) * k, hipMemcpyDeviceToHost, st));
@@ -1122,7 +1123,7 @@ gcss_status gcss_rank_k(gcss_ctx *h, const float *w, int64_t ldw, int32_t l, int
   char *scr = h->at<char>(h->L.scratch);
   HIPCHK(launch_wgram(P, w, ldw, l, n, scr, s));
   {
-    gcss_status g = run_jacobi(h, P, scr);
+    gcss_status g = run_jacobi(h, P, scr, l);
     if (g) return g;
   }
   HIPCHK(launch_rank_outputs(P, scr, l, k, h->at<double>(h->L.Q), h->L.ldq, m, u, ldu, w, ldw, n, v,

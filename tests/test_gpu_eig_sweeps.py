@@ -32,3 +32,26 @@ def test_steep_spectra_converge(gpu, l):
         # eigenvalue, so eps l sweeps, here taken as eps l^2
         assert np.max(np.abs(np.asarray(sigma) ** 2 - np.maximum(want, 0.0))) <= 2.3e-16 * l * l * want[0]
     s.close()
+
+
+@pytest.mark.parametrize("l", [1, 2])
+def test_smallest_embeddings(gpu, l):
+    m, n = 40, 300
+    rng = np.random.default_rng(l)
+    A = np.zeros((n, 64), np.float32)
+    A[:, :m] = rng.standard_normal((n, m))
+    s = gpu.Selector(torch.from_numpy(A).cuda(), m, k_max=l, self_target=True)
+    s.set_target(None)
+    W = torch.zeros(l, n, dtype=torch.float32, device="cuda")
+    s.set_embedding(W)
+    assert s.select(l)[2] == l
+    Q = s.read(gpu.STATE_Q, m * l, np.float64).reshape(l, m)
+    Uw, want, Vt = np.linalg.svd(W.cpu().numpy().astype(np.float64), full_matrices=False)
+    U, sigma, V, _ = s.rank_k(l, l)
+    np.testing.assert_allclose(sigma, want, rtol=1e-14)
+    for j in range(l):
+        u = Uw[:, j] @ Q
+        sign = np.sign(u[np.argmax(np.abs(u))])
+        assert np.max(np.abs(U[j].cpu().numpy() - sign * u)) <= 1e-13
+        assert np.max(np.abs(V[j].cpu().numpy() - sign * Vt[j])) <= 1e-6
+    s.close()
