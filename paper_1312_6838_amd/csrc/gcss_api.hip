@@ -924,12 +924,14 @@ gcss_status gcss_reconstruction_error(gcss_ctx *h, const int64_t *idx, int32_t k
   const bool reuse = h->basis_valid && k <= (int)h->last_idx.size() &&
                      std::equal(v.begin(), v.end(), h->last_idx.begin());
   // A basis the last selection did not build: all columns at once where that
-  // fits the scratch and is certified (from kBasisBlock columns on: its dozen
-  // launches cost what Gram-Schmidt takes for about that many), else
-  // Gram-Schmidt column by column, which drops dependent columns.
+  // fits the scratch and is certified, refined once if need be (from
+  // kBasisBlock columns on: its dozen launches cost what Gram-Schmidt takes for
+  // about that many), else Gram-Schmidt column by column, which drops dependent
+  // columns.
   constexpr int kBasisBlock = 8;
   const BasisPlan bp = basis_plan(m, ldq, k);
   bool block = !reuse && k >= kBasisBlock && k <= m && bp.bytes <= h->L.scratch_bytes;
+  bool refine = false;
   if (!reuse && k > 0) {
     HIPCHK(hipMemcpyAsync(h->at<int64_t>(h->L.pick), v.data(), sizeof(int64_t) * k, hipMemcpyHostToDevice, s));
     h->basis_valid = false;
@@ -940,12 +942,13 @@ gcss_status gcss_reconstruction_error(gcss_ctx *h, const int64_t *idx, int32_t k
       int64_t *pick = h->at<int64_t>(h->L.pick);
       const StepBufs sb = h->bufs(pick, 1);
       // fresh state in basis-only mode
-      HIPCHK(launch_select_begin(h->at<double>(h->L.f0), h->at<double>(h->L.g0), h->at<uint8_t>(h->L.mask0),
-                                 h->at<double>(h->L.f), h->at<double>(h->L.g), h->at<uint8_t>(h->L.mask),
-                                 h->d.n, sb, k, h->d.k_max, h->F0(), kBasisTau, s));
+      if (!refine)
+        HIPCHK(launch_select_begin(h->at<double>(h->L.f0), h->at<double>(h->L.g0), h->at<uint8_t>(h->L.mask0),
+                                   h->at<double>(h->L.f), h->at<double>(h->L.g), h->at<uint8_t>(h->L.mask),
+                                   h->d.n, sb, k, h->d.k_max, h->F0(), kBasisTau, s));
       if (block) {
         HIPCHK(launch_basis(bp, h->at<char>(h->L.scratch), h->A, h->at<double>(h->L.g0), pick, k,
-                            h->at<double>(h->L.Q), ldq, sb.st, h->basis_flag(), s));
+                            h->at<double>(h->L.Q), ldq, refine, sb.st, h->basis_flag(), s));
       } else {
         for (int i = 0; i < k; ++i) HIPCHK(enqueue_basis_step(h, sb));
         DevState hs;
@@ -965,7 +968,9 @@ gcss_status gcss_reconstruction_error(gcss_ctx *h, const int64_t *idx, int32_t k
       // ||A||^2 - sum_s ||A^T q_s||^2; the selection that built this basis
       // already computed the terms exactly (quad), so only a fresh basis needs them
       double *quad = h->at<double>(h->L.quad);
-      if (!reuse) HIPCHK(launch_qta(Q, ldq, kb, nullptr, h->A, (double *)scr, quad, s));
+      // (an uncertified basis has no columns in the state)
+      if (!reuse)
+        HIPCHK(launch_qta(Q, ldq, kb, block ? h->at<DevState>(h->L.st) : nullptr, h->A, (double *)scr, quad, s));
       HIPCHK(launch_gram_err(h->F0(), quad, kb, h->err_dev(), s));
     }
     // the error and, beside it, whether its basis stands (an uncertified one
@@ -976,7 +981,8 @@ gcss_status gcss_reconstruction_error(gcss_ctx *h, const int64_t *idx, int32_t k
     int bad;
     memcpy(&bad, &res[1], sizeof bad);
     if (block && bad) {
-      block = false;
+      refine = bad == kBasisRefine && !refine;
+      block = refine;
       continue;
     }
     *err = res[0];

@@ -252,12 +252,15 @@ struct BasisPlan {
   size_t S, Y, part, W, bytes;
 };
 BasisPlan basis_plan(int64_t m, int64_t ldq, int kmax);
+// What *flag says of a basis: 0 certified, kBasisRefine to be refined, else not
+// to be had this way (the caller then runs Gram-Schmidt).
+constexpr int kBasisBad = 1, kBasisRefine = 2;
 // Q[:, 0..k) = an orthonormal basis of the columns pick[0..k) of A, in their
-// order, state t = k; *flag is 1 where it is not certified (the caller then
-// runs Gram-Schmidt), else 0; norm2: A's squared column norms
+// order (refine: of Q's own), state t = k if it is certified, else 0; norm2:
+// A's squared column norms
 hipError_t launch_basis(const BasisPlan &P, char *scr, const AView &A, const double *norm2,
-                        const int64_t *pick, int k, double *Q, int64_t ldq, DevState *st, int *flag,
-                        hipStream_t s);
+                        const int64_t *pick, int k, double *Q, int64_t ldq, bool refine, DevState *st,
+                        int *flag, hipStream_t s);
 
 // ---- launchers (k_mfma.hip) ----
 // (scratch: parts of f where few columns share their rows' chunks)

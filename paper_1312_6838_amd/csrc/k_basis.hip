@@ -17,7 +17,10 @@
 // takes the deviation to 3/8 E^2.  The result is used only where it is
 // certified: every pivot above kPivotRel of its column's squared norm in A,
 // every |E_ij| <= kDevMax (so ||E||^2 <= 2e-16 for 128 columns), Q^T Y as small.
-// Otherwise (dependent or nearly dependent columns) a flag is set, and the
+// Where only the last two fail, but within kDevRefine (correlated columns, cond
+// 1e3 .. 1e5: about 190 of 2100 us for 100 columns would be lost), the two steps
+// on Y are done once more with Q's chunks as Y, certified by kDevRefined.
+// Otherwise (dependent or nearly dependent columns) the flag says so, and the
 // caller runs Gram-Schmidt, whose rule for dropping columns decides.  (The
 // norm is that of the column as stored, as in that rule: what a chunk's S
 // still holds of a column that depends on earlier chunks is rounding, or an
@@ -40,6 +43,18 @@ constexpr int kBT = 64;   // tile edge
 constexpr int kBK = 32;   // contraction chunk staged in LDS
 constexpr double kPivotRel = 1e-8;
 constexpr double kDevMax = 1e-10;
+// a deviation of kDevRefine becomes 3/8 128 kDevRefine^2 = 1.2e-9 at most, which
+// the second Newton step takes to 3/8 128 (1.5e-9)^2 = 1e-16
+constexpr double kDevRefine = 5e-6;
+constexpr double kDevRefined = 1.5e-9;
+
+// v (a deviation) above `most` spoils the basis, above `ok` it wants refining
+// (by whole waves: one atomic for each).
+__device__ __forceinline__ void bs_check(double v, double ok, double most, int *flag) {
+  const bool bad = !(fabs(v) <= most), fine = fabs(v) <= ok;
+  const int code = (__ballot(bad) ? kBasisBad : 0) | (__ballot(!bad && !fine) ? kBasisRefine : 0);
+  if (code && (threadIdx.x & 63) == 0) atomicOr(flag, code);
+}
 
 __device__ __forceinline__ f64x4 mfma64(double a, double b, f64x4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
@@ -55,6 +70,16 @@ __global__ __launch_bounds__(256) void k_bs_gather(AView A, const int64_t *__res
   const double sc = c < b ? col_scale(A, p) : 0.0;
   const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (j < ldq) S[(int64_t)c * ldq + j] = c < b && j < A.m ? sc * (double)load_elem(A, p, j) : 0.0;
+}
+
+// Y = chunk of b columns of Q, rows m..ldq and columns b.. zero
+__global__ __launch_bounds__(256) void k_bs_take(const double *__restrict__ Q, int64_t m, int b,
+                                                 double *__restrict__ Y, int64_t ldq,
+                                                 int *__restrict__ flag) {
+  const int c = blockIdx.y;
+  if (flag && blockIdx.x == 0 && c == 0 && threadIdx.x == 0) *flag = 0;
+  const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (j < ldq) Y[(int64_t)c * ldq + j] = c < b && j < m ? Q[(int64_t)c * ldq + j] : 0.0;
 }
 
 // Part[z][x][y] = X^T Y over the rows of split z for the 64 x 64 tile of
@@ -121,10 +146,11 @@ __global__ __launch_bounds__(256) void k_bs_tn(const double *__restrict__ X, int
 // W (row-major, 64 ntx x kBC) = the sum over splits of the partial tiles.
 // mode 0: W as it is; 1: W must be small (a second projection's
 // coefficients); 2: W = 3/2 I - 1/2 sum, the sum being near I for the first b
-// columns.  A value outside kDevMax sets the flag.  Grid (elements / 256).
+// columns.  Modes 1 and 2 check the deviation.  Grid (elements / 256).
 __global__ __launch_bounds__(256) void k_bs_reduce(const double *__restrict__ part, int ntx,
-                                                   int nsplit, int mode, int b,
-                                                   double *__restrict__ W, int *__restrict__ flag) {
+                                                   int nsplit, int mode, int b, double ok,
+                                                   double most, double *__restrict__ W,
+                                                   int *__restrict__ flag) {
   constexpr int nty = kBC / kBT;
   const int e = blockIdx.x * 256 + threadIdx.x;  // row-major element of W
   const int i = e / kBC, j = e % kBC;
@@ -142,10 +168,10 @@ __global__ __launch_bounds__(256) void k_bs_reduce(const double *__restrict__ pa
   }
   if (mode == 2) {
     const double id = i == j ? 1.0 : 0.0;
-    if (i < b && j < b && !(fabs(s - id) <= kDevMax)) *flag = 1;
+    bs_check(i < b && j < b ? s - id : 0.0, ok, most, flag);
     W[e] = 1.5 * id - 0.5 * s;
   } else {
-    if (mode == 1 && !(fabs(s) <= kDevMax)) *flag = 1;
+    if (mode == 1) bs_check(s, ok, most, flag);
     W[e] = s;
   }
 }
@@ -153,14 +179,16 @@ __global__ __launch_bounds__(256) void k_bs_reduce(const double *__restrict__ pa
 // out = X W, or in - X W, for the 32 x 64 tile of rows 32 x.. and columns 64
 // y..: X has kx columns, W is row-major with kBC columns.  Only columns < b and
 // rows < m are written.  st: the state of a finished basis of k columns (last
-// chunk).  A FP64 matrix instruction takes 64 cycles of a SIMD, so the tile is
+// chunk; none of it where the flag is set, so that a pass over A for its error
+// has nothing to do).  A FP64 matrix instruction takes 64 cycles of a SIMD, so the tile is
 // kept low (twice the workgroups), and the next chunk's loads are in flight
 // while this one is multiplied: 12.0 -> 7.5 us at m = 1024.
 constexpr int kBR = 32;
 __global__ __launch_bounds__(256) void k_bs_nn(const double *__restrict__ X, int kx,
                                                const double *__restrict__ W,
                                                const double *__restrict__ in, double *out,
-                                               int64_t ldq, int64_t m, int b, DevState *st, int k) {
+                                               int64_t ldq, int64_t m, int b, DevState *st, int k,
+                                               const int *__restrict__ flag) {
   constexpr int PX = kBR + 16, PW = kBT + 16;  // LDS pitches: four rows of 16 doubles, conflict-free
   __shared__ double xs[kBK * PX];  // [k][row]
   __shared__ double ws[kBK * PW];  // [k][column]
@@ -223,7 +251,7 @@ __global__ __launch_bounds__(256) void k_bs_nn(const double *__restrict__ X, int
       }
     }
   if (st && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
-    st->t = k;
+    st->t = *flag ? 0 : k;
     st->pos = k;
   }
 }
@@ -234,7 +262,9 @@ __global__ __launch_bounds__(256) void k_bs_nn(const double *__restrict__ X, int
 // rows below are multiplied by that inverse, the trailing matrix is updated
 // on the matrix cores), then L^-1 from the blocks' inverses by doubling
 // (X21 = -X22 L21 X11 for 16, 32, 64).  A column-at-a-time factorisation
-// would take two barriers and a root per column.
+// would take two barriers and a root per column.  Panels and levels past b are
+// left out (the identity stays): a subset that is handed to Gram-Schmidt has
+// spent this for nothing.
 constexpr int kCP = kBC + 2;  // LDS pitch
 constexpr int kCThreads = 1024;
 
@@ -287,7 +317,9 @@ __global__ __launch_bounds__(kCThreads) void k_bs_chol(const double *__restrict_
   if (threadIdx.x < kBC) g0[threadIdx.x] = (int)threadIdx.x < b ? norm2[pick[threadIdx.x]] : 1.0;
   __syncthreads();
   bool bad = false;
-  for (int p = 0; p < kBC; p += 16) {
+  int nb = 16;  // what of the matrix is worked on: 16, 32, 64 or 128
+  while (nb < b) nb *= 2;
+  for (int p = 0; p < nb; p += 16) {
     double *const d = D + p * 16;
     if (wave == 0) {
       // L of the diagonal block: lane i (of the first 16) holds row i
@@ -326,7 +358,7 @@ __global__ __launch_bounds__(kCThreads) void k_bs_chol(const double *__restrict_
     __syncthreads();
     // rows below: L21 = A21 L11^-T, one thread per (row, column), held until
     // every thread has read A21
-    const int below = kBC - p - 16;
+    const int below = nb - p - 16;
     double lv[2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
@@ -362,18 +394,17 @@ __global__ __launch_bounds__(kCThreads) void k_bs_chol(const double *__restrict_
     }
     __syncthreads();
   }
-  if (wave == 0 && lane < 16 && bad) *flag = 1;
+  if (wave == 0 && lane < 16 && bad) atomicOr(flag, kBasisBad);
   // the diagonal blocks' inverses into place (zero above their diagonals)
-  for (int e = threadIdx.x; e < kBC * 16; e += kCThreads) {
+  for (int e = threadIdx.x; e < nb * 16; e += kCThreads) {
     const int p = e / 256 * 16, i = (e >> 4) & 15, c = e & 15;
     G[(p + i) * kCP + p + c] = c <= i ? D[e] : 0.0;
   }
   __syncthreads();
   // doubling: within blocks of 2s, X21 = -X22 (L21 X11); the product L21 X11
   // is kept in the block's upper right corner
-#pragma unroll
-  for (int s = 16; s < kBC; s *= 2) {
-    const int tp = (s / 16) * (s / 16), pairs = kBC / (2 * s);
+  for (int s = 16; s < nb; s *= 2) {
+    const int tp = (s / 16) * (s / 16), pairs = nb / (2 * s);
     for (int t = wave; t < pairs * tp; t += kCThreads / 64) {
       const int o = (t / tp) * 2 * s, ti = (t % tp) / (s / 16) * 16, tj = (t % tp) % (s / 16) * 16;
       const f64x4 z = {0.0, 0.0, 0.0, 0.0};
@@ -427,12 +458,14 @@ BasisPlan basis_plan(int64_t m, int64_t ldq, int kmax) {
 }
 
 hipError_t launch_basis(const BasisPlan &P, char *scr, const AView &A, const double *norm2,
-                        const int64_t *pick, int k, double *Q, int64_t ldq, DevState *st, int *flag,
-                        hipStream_t s) {
+                        const int64_t *pick, int k, double *Q, int64_t ldq, bool refine, DevState *st,
+                        int *flag, hipStream_t s) {
   const int64_t m = A.m;
   double *S = (double *)(scr + P.S), *Y = (double *)(scr + P.Y), *part = (double *)(scr + P.part),
          *W = (double *)(scr + P.W);
   const unsigned nr = (unsigned)((m + kBR - 1) / kBR), ns = (unsigned)P.nsplit;
+  const dim3 copy((unsigned)((ldq + 255) / 256), kBC);
+  const double ok = refine ? kDevRefined : kDevMax, most = refine ? kDevRefined : kDevRefine;
   auto tn = [&](const double *X, int nx, const double *Z) {
     hipLaunchKernelGGL(k_bs_tn, dim3((unsigned)((nx + kBT - 1) / kBT), kBC / kBT, ns), dim3(256), 0, s,
                        X, nx, Z, ldq, m, P.rows, part);
@@ -440,26 +473,30 @@ hipError_t launch_basis(const BasisPlan &P, char *scr, const AView &A, const dou
   auto reduce = [&](int nx, int mode, int b) {
     const int ntx = (nx + kBT - 1) / kBT;
     hipLaunchKernelGGL(k_bs_reduce, dim3((unsigned)(ntx * kBT * kBC / 256)), dim3(256), 0, s, part,
-                       ntx, P.nsplit, mode, b, W, flag);
+                       ntx, P.nsplit, mode, b, ok, most, W, flag);
   };
   auto nn = [&](const double *X, int kx, const double *in, double *out, int b, DevState *done) {
     hipLaunchKernelGGL(k_bs_nn, dim3(nr, kBC / kBT), dim3(256), 0, s, X, kx, W, in, out, ldq, m, b,
-                       done, k);
+                       done, k, flag);
   };
   for (int t0 = 0; t0 < k; t0 += kBC) {
     const int b = k - t0 < kBC ? k - t0 : kBC;
-    hipLaunchKernelGGL(k_bs_gather, dim3((unsigned)((ldq + 255) / 256), kBC), dim3(256), 0, s, A,
-                       pick + t0, b, S, ldq, t0 == 0 ? flag : nullptr);
-    if (t0 > 0) {
-      tn(Q, t0, S);
-      reduce(t0, 0, b);
-      nn(Q, t0, S, S, kBC, nullptr);
+    double *const Qc = Q + (int64_t)t0 * ldq;
+    if (refine) {
+      hipLaunchKernelGGL(k_bs_take, copy, dim3(256), 0, s, Qc, m, b, Y, ldq, t0 == 0 ? flag : nullptr);
+    } else {
+      hipLaunchKernelGGL(k_bs_gather, copy, dim3(256), 0, s, A, pick + t0, b, S, ldq,
+                         t0 == 0 ? flag : nullptr);
+      if (t0 > 0) {
+        tn(Q, t0, S);
+        reduce(t0, 0, b);
+        nn(Q, t0, S, S, kBC, nullptr);
+      }
+      tn(S, kBC, S);
+      reduce(kBC, 0, b);
+      hipLaunchKernelGGL(k_bs_chol, dim3(1), dim3(kCThreads), 0, s, W, b, pick + t0, norm2, W, flag);
+      nn(S, kBC, nullptr, Y, kBC, nullptr);
     }
-    tn(S, kBC, S);
-    reduce(kBC, 0, b);
-    hipLaunchKernelGGL(k_bs_chol, dim3(1), dim3(kCThreads), 0, s, W, b, pick + t0, norm2, W,
-                       flag);
-    nn(S, kBC, nullptr, Y, kBC, nullptr);
     if (t0 > 0) {
       tn(Q, t0, Y);
       reduce(t0, 1, b);
@@ -467,7 +504,7 @@ hipError_t launch_basis(const BasisPlan &P, char *scr, const AView &A, const dou
     }
     tn(Y, kBC, Y);
     reduce(kBC, 2, b);
-    nn(Y, kBC, nullptr, Q + (int64_t)t0 * ldq, b, t0 + b == k ? st : nullptr);
+    nn(Y, kBC, nullptr, Qc, b, t0 + b == k ? st : nullptr);
     hipError_t e = hipGetLastError();
     if (e) return e;
   }
