@@ -72,7 +72,8 @@ typedef struct {
   int32_t reserved;        /* must be 0                                              */
   double tau;              /* eligibility threshold: a column stays a candidate while
                               g_i > tau * g0_i (g = squared norm of its residual);
-                              <= 0 selects 1e-4                                      */
+                              <= 0 selects 1e-4 (below 1e-6 a step takes 5 to 15 us
+                              more, for two projections in FP64)                     */
   void *stream;            /* hipStream_t for all work of the context; NULL = default */
 } gcss_desc;
 
@@ -197,9 +198,12 @@ gcss_status gcss_select_async(gcss_ctx *h, int32_t k, int64_t *d_idx, double *d_
 /*
  * Reconstruction error || B - P_S B ||_F^2 of the current target for the
  * columns S = idx[0..k-1] (host, distinct, in [0, n)), written to *err
- * (host).  P_S comes from an FP64 Gram-Schmidt basis Q (with one
- * re-orthogonalisation) of A_S; a column numerically dependent on the
- * earlier ones adds no direction.  For an explicit B the residual
+ * (host).  P_S comes from an orthonormal FP64 basis Q of A_S: the last
+ * selection's if it made these picks, else one formed from all columns at
+ * once (Cholesky QR with a Newton step) where it is certified orthonormal,
+ * else Gram-Schmidt with one re-orthogonalisation.  A column numerically
+ * dependent on the earlier ones (its residual's squared norm at most 1e-13 of
+ * its own) adds no direction.  For an explicit B the residual
  * B - Q (Q^T B) is formed and summed in FP64.  For B = A the error is
  * ||A||_F^2 - sum_s ||A^T q_s||^2 with FP64 products and sums.
  * Errors: GCSS_ERR_ARG, GCSS_ERR_STATE, GCSS_ERR_DEVICE.

@@ -131,6 +131,8 @@ __global__ __launch_bounds__(256) void k_stream_b(AView A, const GroupEnt *__res
       tau = st->tau;
       if (ws == 0) {
         const int64_t colc = col0 + (lane < ncol ? lane : 0);
+        // (scores past the caches also where A fits them: over eight problems of
+        // 2 to 197 MB a call takes 0.986 to 1.006 of its time with cached ones)
         fv = __builtin_nontemporal_load(f + colc);
         gv = __builtin_nontemporal_load(g + colc);
         g0v = __builtin_nontemporal_load(g0 + colc);
