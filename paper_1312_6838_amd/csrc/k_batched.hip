@@ -418,10 +418,10 @@ typedef void (*BStreamFn)(AView, const GroupEnt *, int64_t, const float *, const
 
 template <int DT, int NJ>
 static BStreamFn bpick_w(int w) {
-  switch (w) {
-    case 1: return k_stream_b<DT, NJ, 1>;
-    case 2: return k_stream_b<DT, NJ, 2>;
-    case 4: return k_stream_b<DT, NJ, 4>;
+  if (w == 1) return k_stream_b<DT, NJ, 1>;
+  if constexpr (NJ * BElem<DT>::epc == 32) {  // (as in the single pass)
+    if (w == 2) return k_stream_b<DT, NJ, 2>;
+    if (w == 4) return k_stream_b<DT, NJ, 4>;
   }
   return nullptr;
 }

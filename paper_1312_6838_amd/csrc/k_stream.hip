@@ -501,12 +501,14 @@ static StreamFn pick_pd(int pd, bool big) {
   return pd >= 2 ? (StreamFn)k_stream<DT, NJ, W, 2, EX, false> : (StreamFn)k_stream<DT, NJ, W, 1, EX, false>;
 }
 
+// (several waves share a column only once one's registers are full: 32
+// elements a lane; half the instances and of the compile time of all shapes)
 template <int DT, int NJ, bool EX>
 static StreamFn pick_w(int w, int pd, bool big) {
-  switch (w) {
-    case 1: return pick_pd<DT, NJ, 1, EX>(pd, big);
-    case 2: return pick_pd<DT, NJ, 2, EX>(pd, big);
-    case 4: return pick_pd<DT, NJ, 4, EX>(pd, big);
+  if (w == 1) return pick_pd<DT, NJ, 1, EX>(pd, big);
+  if constexpr (NJ * Elem<DT>::epc == 32) {
+    if (w == 2) return pick_pd<DT, NJ, 2, EX>(pd, big);
+    if (w == 4) return pick_pd<DT, NJ, 4, EX>(pd, big);
   }
   return nullptr;
 }
