@@ -927,10 +927,12 @@ gcss_status gcss_reconstruction_error(gcss_ctx *h, const int64_t *idx, int32_t k
   // fits the scratch and is certified, refined once if need be (from
   // kBasisBlock columns on: its dozen launches cost what Gram-Schmidt takes for
   // about that many), else Gram-Schmidt column by column, which drops dependent
-  // columns.
+  // columns (a small subset's in one launch, so that the attempt before it costs
+  // such a subset nothing in all).
   constexpr int kBasisBlock = 8;
   const BasisPlan bp = basis_plan(m, ldq, k);
   bool block = !reuse && k >= kBasisBlock && k <= m && bp.bytes <= h->L.scratch_bytes;
+  const bool tried = block;
   bool refine = false;
   if (!reuse && k > 0) {
     HIPCHK(hipMemcpyAsync(h->at<int64_t>(h->L.pick), v.data(), sizeof(int64_t) * k, hipMemcpyHostToDevice, s));
@@ -949,6 +951,9 @@ gcss_status gcss_reconstruction_error(gcss_ctx *h, const int64_t *idx, int32_t k
       if (block) {
         HIPCHK(launch_basis(bp, h->at<char>(h->L.scratch), h->A, h->at<double>(h->L.g0), pick, k,
                             h->at<double>(h->L.Q), ldq, refine, sb.st, h->basis_flag(), s));
+      } else if (tried && gs_subset_fits(m, k)) {
+        HIPCHK(launch_gs_subset(h->A, pick, k, h->at<double>(h->L.g0), kBasisTau, h->at<double>(h->L.Q),
+                                ldq, sb.st, s));
       } else {
         for (int i = 0; i < k; ++i) HIPCHK(enqueue_basis_step(h, sb));
         DevState hs;

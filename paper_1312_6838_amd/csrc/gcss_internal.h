@@ -262,6 +262,13 @@ hipError_t launch_basis(const BasisPlan &P, char *scr, const AView &A, const dou
                         const int64_t *pick, int k, double *Q, int64_t ldq, bool refine, DevState *st,
                         int *flag, hipStream_t s);
 
+// The same column by column in one workgroup (k_chain.hip): a column whose
+// residual's squared norm is at most tau of its own adds nothing; state t = the
+// columns kept, the rest of Q's k columns zero
+bool gs_subset_fits(int64_t m, int k);
+hipError_t launch_gs_subset(const AView &A, const int64_t *pick, int k, const double *norm2,
+                            double tau, double *Q, int64_t ldq, DevState *st, hipStream_t s);
+
 // ---- launchers (k_mfma.hip) ----
 // (scratch: parts of f where few columns share their rows' chunks)
 // f0_i = scale_i^2 * || X^T A_i ||^2 (X: m x R, K-contiguous, ldx), g0_i, mask0_i

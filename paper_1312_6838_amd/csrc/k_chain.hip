@@ -1016,6 +1016,65 @@ __global__ __launch_bounds__(kBlkThreads) void k_chain_one(ChainArgs ca, AView A
   }
 }
 
+// Gram-Schmidt of a small subset of A's columns, pick[0..k), in one workgroup:
+// each column twice against the t kept before it, kept where its residual's
+// squared norm is above tau of its own (norm2) as in the general kernels, which
+// take four launches a column (18 us).  One CU reads Q's t columns four times
+// for the next, so this serves m k <= 48 K: with the attempt at all columns at
+// once before it, general kernels -> this: m 333, k 10 340 -> 228 us; 1024, 32
+// about 740 -> 600; 700, 64 1365 -> 1240; but 1024, 64 1390 -> 1500 and 2048,
+// 64 1550 -> 2490.  Columns t..k of Q are zero at the end.
+__global__ __launch_bounds__(kBlkThreads) void k_gs_subset(AView A, const int64_t *__restrict__ pick,
+                                                           int k, const double *__restrict__ norm2,
+                                                           double tau, double *Q, int64_t ldq,
+                                                           DevState *st) {
+  extern __shared__ double lds[];  // vec (m), coefficients (k)
+  __shared__ double wsum[kBlkWaves];
+  const int64_t m = A.m;
+  double *vec = lds, *cf = lds + m;
+  int t = 0;
+  for (int x = 0; x < k; ++x) {
+    const int64_t p = pick[x];
+    const double ps = col_scale(A, p);
+    for (int64_t j = threadIdx.x; j < m; j += kBlkThreads) vec[j] = ps * (double)load_elem(A, p, j);
+    __syncthreads();
+    double nrm2 = 0.0;
+    for (int pass = 0; pass < 2; ++pass) {
+      blk_dots((const double *)Q, ldq, t, vec, m, cf);
+      __syncthreads();
+      double sq = 0.0;
+      for (int64_t j = threadIdx.x; j < m; j += kBlkThreads) {
+        const double e = vec[j] - blk_row((const double *)Q, ldq, t, j, cf);
+        vec[j] = e;
+        sq = fma(e, e, sq);
+      }
+      __syncthreads();
+      if (pass == 1) nrm2 = blk_sum(sq, wsum);
+    }
+    if (isfinite(nrm2) && nrm2 > tau * norm2[p]) {  // (the same in every thread)
+      const double inv = 1.0 / sqrt(nrm2);
+      for (int64_t j = threadIdx.x; j < m; j += kBlkThreads) Q[(int64_t)t * ldq + j] = vec[j] * inv;
+      ++t;
+    }
+    __syncthreads();  // the new column, for every wave's next dots
+  }
+  for (int x = t; x < k; ++x)
+    for (int64_t j = threadIdx.x; j < m; j += kBlkThreads) Q[(int64_t)x * ldq + j] = 0.0;
+  if (threadIdx.x == 0) {
+    st->t = t;
+    st->pos = k;
+  }
+}
+
+bool gs_subset_fits(int64_t m, int k) { return m <= kBlkMaxM && k <= 256 && m * k <= 48 * 1024; }
+
+hipError_t launch_gs_subset(const AView &A, const int64_t *pick, int k, const double *norm2,
+                            double tau, double *Q, int64_t ldq, DevState *st, hipStream_t s) {
+  hipLaunchKernelGGL(k_gs_subset, dim3(1), dim3(kBlkThreads), (size_t)(A.m + k) * sizeof(double), s, A,
+                     pick, k, norm2, tau, Q, ldq, st);
+  return hipGetLastError();
+}
+
 size_t chain_block_lds_bytes(int64_t m, int64_t r, int kmax) {
   return (size_t)(m + kmax + 1 + r) * sizeof(double);
 }
